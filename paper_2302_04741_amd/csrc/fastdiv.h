@@ -1,5 +1,6 @@
-// Unsigned 32-bit division by a divisor fixed at launch; no HIP dependency
-// (the host builds the constants, the kernels divide, a CPU test checks it).
+// Index arithmetic of the kernels: unsigned 32-bit division by a divisor fixed at
+// launch, and the periodic wrap of a streaming shift; no HIP dependency (CPU tests
+// check both).
 #pragma once
 
 #include <stdint.h>
@@ -30,6 +31,25 @@ __host__ __device__ inline uint32_t divu(const DivU32 &q, uint32_t n)
 {
     const uint32_t t = uint32_t((uint64_t(n) * q.m) >> 32);  // mulhi(n, m)
     return (t + ((n - t) >> q.s1)) >> q.s2;
+}
+
+// d mod n for a shift d of 1..3 nodes and any n >= 1
+__host__ __device__ inline uint32_t shift_mod(uint32_t d, uint32_t n)
+{
+    return d < n ? d : (n == 2 ? d & 1u : 0u);
+}
+
+// (v - d) mod n for v in [0, n), |d| <= 3, 1 <= n <= 2^31: the shift is taken
+// modulo n first (on the scalar unit), so one correction is left, and of its two
+// candidates the unsigned smaller is the one in [0, n).  No branch: a loop or a
+// test on n < 4 here cost a wavefront some 40 instructions for each of 14 shifts.
+__host__ __device__ inline uint32_t wrap_back(uint32_t v, int d, uint32_t n)
+{
+    if (d == 0) return v;
+    const uint32_t m = shift_mod(uint32_t(d < 0 ? -d : d), n);
+    const uint32_t s = d > 0 ? v - m : v + m;
+    const uint32_t t = d > 0 ? s + n : s - n;
+    return s < t ? s : t;
 }
 
 }  // namespace lbm

@@ -9,9 +9,9 @@
 //   force       = Hermite expansion eq. (F) to the third moment, eq. (fi);
 //   sigma-bar   = -(1 - 1/(2 tau^)) sum_i (f~_i - f0_i)(xi_i - u)(xi_i - u), traceless;
 //   step        = eq. (lbm): f~(x + xi_i, t+1) = f~ - (f~ - f0)/tau^ + (1 - 1/(2 tau^)) F.
-// Everything here is written as closed-form polynomials in xi.u, xi.g and
-// xi.sigma.xi with per-shell constants, and shares the even/odd parts of each
-// +c/-c velocity pair.
+// Everything here is written as closed-form polynomials in the integer velocity
+// components with per-cell coefficients, and shares the sign parts of each orbit
+// of velocities that differ in signs only.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,9 +42,9 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // ---------------------------------------------------------------------------
-// buffer access to one population plane: scalar resource (plane base, size),
-// scalar row offset, per-lane 32-bit x offset.  Addressing costs no VALU
-// work, and the hardware range check drops accesses past the plane.
+// buffer access to the population planes: scalar resource (plane base, size),
+// scalar row offset, per-lane 32-bit x offset.  Addressing costs no VALU work,
+// and the hardware range check drops accesses past the plane.
 // ---------------------------------------------------------------------------
 constexpr int BUF_DWORD3 = 0x00020000;  // raw buffer, 32-bit data format
 // Cache policy of the step's population traffic.  Every element is read once
@@ -54,50 +54,69 @@ constexpr int BUF_DWORD3 = 0x00020000;  // raw buffer, 32-bit data format
 constexpr int BUF_LD = 0;
 constexpr int BUF_NT = 2;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, int(bytes),
-                                             BUF_DWORD3);
-}
+typedef int RsrcWords __attribute__((ext_vector_type(4)));
+typedef int Words2 __attribute__((ext_vector_type(2)));
+__device__ float buf_load_f32(RsrcWords, int, int, int) __asm("llvm.amdgcn.raw.buffer.load.f32");
+__device__ Words2 buf_load_2i32(RsrcWords, int, int, int) __asm("llvm.amdgcn.raw.buffer.load.v2i32");
+__device__ short buf_load_i16(RsrcWords, int, int, int) __asm("llvm.amdgcn.raw.buffer.load.i16");
+__device__ void buf_store_f32(float, RsrcWords, int, int,
+                              int) __asm("llvm.amdgcn.raw.buffer.store.f32");
+__device__ void buf_store_2i32(Words2, RsrcWords, int, int,
+                               int) __asm("llvm.amdgcn.raw.buffer.store.v2i32");
+__device__ void buf_store_i16(short, RsrcWords, int, int,
+                              int) __asm("llvm.amdgcn.raw.buffer.store.i16");
+
+// The planes of one population buffer, one after the other: the next plane's
+// resource is two scalar adds away from the last one's (a resource made afresh
+// for each plane took about ten scalar instructions, and a wavefront issues one
+// scalar instruction in the time of one vector instruction).
+struct PlaneWalk {
+    uint64_t base;  // device address of the current plane (48 bits)
+    uint32_t bytes;
+    int plane;
+    __device__ __forceinline__ PlaneWalk(const void *p, uint32_t plane_bytes)
+        : base(reinterpret_cast<uint64_t>(p)), bytes(plane_bytes), plane(0)
+    {
+    }
+    // resource of plane i (a compile-time index)
+    __device__ __forceinline__ RsrcWords at(int i)
+    {
+        if (i >= plane) base += uint64_t(bytes) * uint32_t(i - plane);
+        else base -= uint64_t(bytes) * uint32_t(plane - i);
+        plane = i;
+        return RsrcWords{int(uint32_t(base)), int(uint32_t(base >> 32)), int(bytes), BUF_DWORD3};
+    }
+};
 
 template <class S> struct BufIO;
 template <> struct BufIO<float> {
-    __device__ static __forceinline__ float load(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t s)
+    __device__ static __forceinline__ float load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return __builtin_bit_cast(float,
-                                  __builtin_amdgcn_raw_buffer_load_b32(r, int(v), int(s), BUF_LD));
+        return buf_load_f32(r, int(v), int(s), BUF_LD);
     }
-    __device__ static __forceinline__ void store(float x, __amdgpu_buffer_rsrc_t r, uint32_t v,
-                                                 uint32_t s)
+    __device__ static __forceinline__ void store(float x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, int(v), int(s),
-                                              BUF_NT);
+        buf_store_f32(x, r, int(v), int(s), BUF_NT);
     }
 };
 template <> struct BufIO<double> {
-    __device__ static __forceinline__ double load(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t s)
+    __device__ static __forceinline__ double load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return __builtin_bit_cast(double,
-                                  __builtin_amdgcn_raw_buffer_load_b64(r, int(v), int(s), BUF_LD));
+        return __builtin_bit_cast(double, buf_load_2i32(r, int(v), int(s), BUF_LD));
     }
-    __device__ static __forceinline__ void store(double x, __amdgpu_buffer_rsrc_t r, uint32_t v,
-                                                 uint32_t s)
+    __device__ static __forceinline__ void store(double x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        using V2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V2, x), r, int(v), int(s), BUF_NT);
+        buf_store_2i32(__builtin_bit_cast(Words2, x), r, int(v), int(s), BUF_NT);
     }
 };
 template <> struct BufIO<__half> {
-    __device__ static __forceinline__ __half load(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t s)
+    __device__ static __forceinline__ __half load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return __builtin_bit_cast(__half,
-                                  __builtin_amdgcn_raw_buffer_load_b16(r, int(v), int(s), BUF_LD));
+        return __builtin_bit_cast(__half, buf_load_i16(r, int(v), int(s), BUF_LD));
     }
-    __device__ static __forceinline__ void store(__half x, __amdgpu_buffer_rsrc_t r, uint32_t v,
-                                                 uint32_t s)
+    __device__ static __forceinline__ void store(__half x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x), r, int(v),
-                                              int(s), BUF_NT);
+        buf_store_i16(__builtin_bit_cast(short, x), r, int(v), int(s), BUF_NT);
     }
 };
 
@@ -127,6 +146,44 @@ template <class L> constexpr int c2(int i)
 {
     return L::c(i, 0) * L::c(i, 0) + L::c(i, 1) * L::c(i, 1) + L::c(i, 2) * L::c(i, 2);
 }
+
+// Velocities come in orbits of sign flips: |c| = (k_x, k_y, k_z) with every sign
+// of every nonzero component, 2, 4 or 8 velocities of one shell.  orbit_rep: i
+// is the orbit's member without negative components; velocity_of: the index of
+// a vector of the set.
+template <class L> constexpr bool orbit_rep(int i)
+{
+    return i > 0 && L::c(i, 0) >= 0 && L::c(i, 1) >= 0 && L::c(i, 2) >= 0;
+}
+template <class L> constexpr int velocity_of(int x, int y, int z)
+{
+    for (int i = 0; i < L::Q; ++i)
+        if (L::c(i, 0) == x && L::c(i, 1) == y && L::c(i, 2) == z) return i;
+    return -1;
+}
+template <class L> constexpr int opposite(int i)
+{
+    return velocity_of<L>(-L::c(i, 0), -L::c(i, 1), -L::c(i, 2));
+}
+// The orbit of rep seen as +c/-c pairs: pair s flips the sign of the last nonzero
+// axis by bit 0 of s and, of three, that of the second by bit 1; the planes of
+// the pairs then ascend.
+template <class L> struct Orbit {
+    int n, ax[3];  // nonzero components and their axes
+    constexpr explicit Orbit(int rep) : n(0), ax{0, 0, 0}
+    {
+        for (int a = 0; a < 3; ++a)
+            if (L::c(rep, a) != 0) ax[n++] = a;
+    }
+    constexpr int pairs() const { return n == 1 ? 1 : (n == 2 ? 2 : 4); }
+    constexpr int plus(int rep, int s) const
+    {
+        int c[3] = {L::c(rep, 0), L::c(rep, 1), L::c(rep, 2)};
+        if (n > 1 && (s & 1)) c[ax[n - 1]] = -c[ax[n - 1]];
+        if (s & 2) c[ax[1]] = -c[ax[1]];
+        return velocity_of<L>(c[0], c[1], c[2]);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // storage conversion
@@ -236,19 +293,6 @@ struct TileSim {
     WallDesc wd;         // plates (off for a periodic member); wd.par is set per step
 };
 
-// Periodic wrap of v in [-3, n + 3) into [0, n), valid for any n >= 1.
-__device__ __forceinline__ int wrap3(int v, int n)
-{
-    if (n >= 4) {
-        v += (v < 0) ? n : 0;
-        v -= (v >= n) ? n : 0;
-        return v;
-    }
-    while (v < 0) v += n;
-    while (v >= n) v -= n;
-    return v;
-}
-
 // ---------------------------------------------------------------------------
 // body force at a cell
 // ---------------------------------------------------------------------------
@@ -296,44 +340,78 @@ template <class T> struct RawSums {
 //
 // SC::scale<i>() is the factor the values carry (1, or the power of two of
 // reduced-precision storage, the same for every velocity of a shell): the
-// sums take it out through their constants, so scaled and unscaled inputs
-// give bitwise the same sums.
+// sums take it out through their constants.
+//
+// The sums go orbit by orbit: the 2, 4 or 8 populations of an orbit are first
+// transformed into their sign sums (a Hadamard transform: S = sum, X_a = sum
+// sign_a, E_ab = sum sign_a sign_b), of which each moment needs one term per
+// orbit; the diagonal of P shares its running sums by |c_a| = 1, 2, 3.
 template <class L, class T, class SC = UnitScale>
 __device__ __forceinline__ RawSums<T> raw_sums(const T (&h)[L::Q])
 {
+    constexpr int D = L::D;
     RawSums<T> s;
-    constexpr double u0 = 1.0 / SC::template scale<0>();
-    s.drho = (u0 == 1.0) ? h[0] : h[0] * T(u0);
     for (int a = 0; a < 3; ++a) {
         s.j[a] = T(0);
         for (int b = 0; b < 3; ++b) s.P[a][b] = T(0);
     }
-    static_for<0, (L::Q - 1) / 2>([&](auto K) {
-        constexpr int ip = 1 + 2 * decltype(K)::value;
-        constexpr int im = ip + 1;
-        static_assert(SC::template scale<ip>() == SC::template scale<im>(),
-                      "a pair shares its scale");
-        constexpr double u = 1.0 / SC::template scale<ip>();  // exact: a power of two
-        const T sp = h[ip] + h[im];
-        const T dm = h[ip] - h[im];
-        // acc += m * v with the scale folded into m: one rounding, as unscaled
-        auto add = [&](T &acc, int m, T v) {
-            if (u == 1.0 && m == 1) acc += v;
-            else if (u == 1.0 && m == -1) acc -= v;
-            else acc = fma_t(v, T(m * u), acc);
-        };
-        add(s.drho, 1, sp);
-        static_for<0, L::D>([&](auto A) {
-            constexpr int a = decltype(A)::value;
-            constexpr int ca = L::c(ip, a);
-            if constexpr (ca != 0) add(s.j[a], ca, dm);
-            static_for<a, L::D>([&](auto B) {
-                constexpr int b = decltype(B)::value;
-                constexpr int cab = ca * L::c(ip, b);
-                if constexpr (cab != 0) add(s.P[a][b], cab, sp);
+    T by_k[3][3];  // [axis][|c_a| - 1]: sum of the orbits' S
+    T rest;        // orbits without an x component
+    for (int a = 0; a < 3; ++a)
+        for (int k = 0; k < 3; ++k) by_k[a][k] = T(0);
+    constexpr double u0 = 1.0 / SC::template scale<0>();
+    rest = (u0 == 1.0) ? h[0] : h[0] * T(u0);
+    // acc += m * v, one rounding; the scale is folded into m
+    auto add = [](T &acc, double m, T v) {
+        if (m == 1.0) acc += v;
+        else acc = fma_t(v, T(m), acc);
+    };
+    static_for<1, L::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (orbit_rep<L>(i)) {
+            constexpr Orbit<L> o(i);
+            constexpr double u = 1.0 / SC::template scale<i>();  // exact: a power of two
+            constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
+            constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
+            T sp[4], dm[4];
+            static_for<0, o.pairs()>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                constexpr int ip = o.plus(i, j);
+                constexpr int im = opposite<L>(ip);
+                sp[j] = h[ip] + h[im];
+                dm[j] = h[ip] - h[im];
             });
-        });
+            T S;
+            if constexpr (o.n == 1) {
+                S = sp[0];
+                add(s.j[a0], u * k0, dm[0]);
+            } else if constexpr (o.n == 2) {
+                S = sp[0] + sp[1];
+                add(s.P[a0][a1], u * (k0 * k1), sp[0] - sp[1]);
+                add(s.j[a0], u * k0, dm[0] + dm[1]);
+                add(s.j[a1], u * k1, dm[0] - dm[1]);
+            } else {
+                const T pa = sp[0] + sp[1], ma = sp[0] - sp[1];
+                const T pb = sp[2] + sp[3], mb = sp[2] - sp[3];
+                S = pa + pb;
+                add(s.P[a0][a2], u * (k0 * k2), ma + mb);
+                add(s.P[a0][a1], u * (k0 * k1), pa - pb);
+                add(s.P[a1][a2], u * (k1 * k2), ma - mb);
+                const T qa = dm[0] + dm[1], na = dm[0] - dm[1];
+                const T qb = dm[2] + dm[3], nb = dm[2] - dm[3];
+                add(s.j[a0], u * k0, qa + qb);
+                add(s.j[a2], u * k2, na + nb);
+                add(s.j[a1], u * k1, qa - qb);
+            }
+            add(by_k[a0][k0 - 1], u, S);
+            if constexpr (o.n >= 2) add(by_k[a1][k1 - 1], u, S);
+            if constexpr (o.n >= 3) add(by_k[a2][k2 - 1], u, S);
+            if constexpr (L::c(i, 0) == 0) add(rest, u, S);
+        }
     });
+    s.drho = rest + ((by_k[0][0] + by_k[0][1]) + by_k[0][2]);
+    for (int a = 0; a < D; ++a)
+        s.P[a][a] = fma_t(T(9), by_k[a][2], fma_t(T(4), by_k[a][1], by_k[a][0]));
     return s;
 }
 
@@ -411,171 +489,218 @@ __device__ __forceinline__ void finish_moments(const RawSums<T> &s, const T g[3]
 //     odd part  w rho xg                                       (order 1, 2)
 //               w rho [xg (1 + (xu^2 - u2 + t(X2 - D - 2))/2) - gu xu]   (order >= 3)
 //               - (w/2) [xg (xi.sigma.xi) - 2 xi.sigma.g]     (order 4)
-// With NO_BASE the even part omits alpha * w * rho (the leading term of f0),
-// so that callers can add it as an exactly rounded increment.  With a scale
-// SC every w is w * SC::scale<i>() (a power of two): even and odd come out
-// multiplied by it exactly.
+// With NO_BASE the even part omits alpha * w * rho (the leading term of f0);
+// w * base is added to it (callers pass the exactly rounded increment of that
+// leading term).  With a scale SC every w is w * SC::scale<i>() (a power of
+// two): even and odd come out multiplied by it exactly.
 // The callback receives (i_plus, i_minus, even, odd) for each pair and
 // (0, -1, even, 0) for the rest velocity; the indices are passed as
 // std::integral_constant so that callers index register arrays statically.
+//
+// Evaluation.  In the integer components c of xi = r c, even/w and odd/w are
+// polynomials of degree <= 4 whose coefficients depend on the cell only, so
+// they are computed once a cell and each orbit of sign flips needs its sign
+// parts only: with |c| = (k_x, k_y, k_z)
+//   even/w = E + sum_{a<b} sign_a sign_b E_ab,  odd/w = sum_a sign_a O_a (+ sign_xyz O_xyz),
+//   E    = C + sum_a k_a^2 (K_a + k_a^2 Q_a) + k_x^2 k_y^2 Q_xy      (Q: N = 4, D = 2)
+//   E_ab = k_a k_b (K_ab + k_a^2 Q_aab + k_b^2 Q_abb)
+//   O_a  = k_a (G_a + sum_b k_b^2 H_ab),   O_xyz = k_x k_y k_z H_xyz
+// and the 2, 4 or 8 velocities of the orbit are the butterflies of those parts.
+// Against xi.u, xi.g and xi.sigma.xi dotted out for each pair this halves the
+// step's vector instructions (counts and times at step_cell).
 // ---------------------------------------------------------------------------
 template <class L, class T, int EQ, int FO, bool NO_BASE = false, class SC = UnitScale,
           class CB>
-__device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T beta, CB &&cb)
+__device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T beta, T base,
+                                            CB &&cb)
 {
     constexpr int D = L::D;
+    static_assert(EQ < 4 || D == 2, "the fourth order is written out for two dimensions");
     const T r = T(L::R), r2 = T(L::R2);
-    T ur[3], gr[3], hr[3], sr[3][3];
-    T u2 = T(0), gu = T(0);
+    T U[3], G[3], u2 = T(0), gu = T(0);
     for (int a = 0; a < 3; ++a) {
-        ur[a] = r * cs.ub[a];
-        gr[a] = r * cs.g[a];
-        hr[a] = T(0);
+        U[a] = r * cs.ub[a];
+        G[a] = r * cs.g[a];
     }
     for (int a = 0; a < D; ++a) {
-        u2 += cs.ub[a] * cs.ub[a];
-        gu += cs.g[a] * cs.ub[a];
-    }
-    if constexpr (FO == 4) {
-        for (int a = 0; a < D; ++a) {
-            T h = T(0);
-            for (int b = 0; b < D; ++b) {
-                h += cs.sig[a][b] * cs.g[b];
-                sr[a][b] = r2 * cs.sig[a][b];
-            }
-            hr[a] = r * h;
-        }
+        u2 = fma_t(cs.ub[a], cs.ub[a], u2);
+        gu = fma_t(cs.g[a], cs.ub[a], gu);
     }
     const T t = cs.th - T(1);
-    const T rho = cs.rho;
-
-    // The shell constants below are polynomials in the shell's X2 = |xi|^2 (a
-    // compile-time value) with coefficients that depend on the cell only:
-    // computed once here, each shell then costs a Horner step per polynomial.
-    //   e0 - 1 (the even constant without its leading 1) = E0 + E1 X2 + E2 X2^2
-    //   e1 (even, times xu^2)                             = D0 + D1 X2
-    //   o0 (odd, times xu)                                = G0 + G1 X2
+    const T arho = alpha * cs.rho, brho = beta * cs.rho, brgu = brho * gu;
     const T half_t = T(0.5) * t;
-    T E0 = T(-0.5) * (t * T(D) + u2), E1 = half_t, E2 = T(0);
+
+    // polynomials in X2 of the even part's constant E0 + E1 X2 + E2 X2^2, of its
+    // xu^2 factor D0 + D1 X2, and of the odd part's xu factor G0 + G1 X2
+    T E0 = T(-0.5) * fma_t(T(D), t, u2), E1 = half_t, E2 = T(0);
     T D0 = T(0.5), D1 = T(0);
     if constexpr (!NO_BASE) E0 += T(1);
     if constexpr (EQ == 4) {
         // [3 u2^2 + 6 t u2 (D + 2 - X2) + 3 t^2 (X2^2 - 2 (D + 2) X2 + D (D + 2))] / 24
         const T tt = t * t;
-        E0 += T(0.125) * u2 * u2 + T(0.25 * (D + 2)) * t * u2 + T(0.125 * D * (D + 2)) * tt;
-        E1 -= T(0.25) * (t * u2 + T(D + 2) * tt);
+        const T tu = t * u2;
+        E0 += fma_t(T(0.125) * u2, u2, fma_t(T(0.25 * (D + 2)), tu, T(0.125 * D * (D + 2)) * tt));
+        E1 -= T(0.25) * fma_t(T(D + 2), tt, tu);
         E2 = T(0.125) * tt;
         // (t (X2 - D - 4) - u2) / 4
-        D0 -= T(0.25) * (t * T(D + 4) + u2);
+        D0 -= T(0.25) * fma_t(T(D + 4), t, u2);
         D1 = T(0.25) * t;
     }
-    const T G0 = T(1) - T(0.5) * u2 - half_t * T(D + 2), G1 = half_t;
-    const T arho = alpha * rho;  // A = ws arho multiplies the equilibrium bracket
-    const T brho = beta * rho;   // Bf = ws brho multiplies the force bracket
-    const T brgu = brho * gu;
-    const T hbeta = T(0.5) * beta;
+    const T G0 = T(1) - fma_t(half_t, T(D + 2), T(0.5) * u2), G1 = half_t;
 
-    // per-shell constants, recomputed at the first pair of each shell
-    T K0 = T(0), Ka = T(0), Kq = T(0), K6 = T(0), Kb = T(0), Kb2 = T(0), Kw = T(0), K24 = T(0);
-    T Kbf = T(0);
-    auto shell_consts = [&](auto S) {
-        constexpr int s = decltype(S)::value;
-        // any velocity of the shell gives X2
-        constexpr int iref = [] {
-            int i = 0;
-            while (L::shell(i) != s) ++i;
-            return i;
-        }();
-        const T X2 = T(L::R2 * c2<L>(iref));
-        // the shell's weight times the scale its values carry (a power of two):
-        // every constant below is linear in it, so even and odd come out
-        // scaled, rounding for rounding
-        const T ws = T(L::wshell(s) * SC::template scale<iref>());
-        const T A = ws * arho;
-        const T Bf = ws * brho;
-        const T e0t = (EQ == 4) ? fma_t(fma_t(E2, X2, E1), X2, E0) : fma_t(E1, X2, E0);
-        const T o0 = fma_t(G1, X2, G0);
-        if constexpr (FO >= 2) K0 = ws * fma_t(arho, e0t, -brgu);  // A e0 - Bf gu
-        else K0 = A * e0t;
-        Ka = (EQ == 4) ? A * fma_t(D1, X2, D0) : A * T(0.5);
-        if constexpr (EQ >= 3) {
-            Kq = (FO >= 3) ? ws * fma_t(arho, o0, -brgu) : A * o0;  // odd, times xu
-            K6 = A * T(1.0 / 6.0);                                   // odd, times xu^3
-        } else {
-            Kq = (FO >= 3) ? ws * (arho - brgu) : A;
-            K6 = T(0);
+    // even coefficients
+    T C = fma_t(arho, E0, base);
+    if constexpr (FO >= 2) C -= brgu;
+    T K[3], Kab[3][3], Q[3] = {T(0), T(0), T(0)}, Qxy = T(0), Qab[2] = {T(0), T(0)};
+    {
+        const T e1 = arho * E1 * r2;
+        const T m = arho * D0;
+        T V[3];  // half the quadratic form's vector: K_ab = U_a V_b + U_b V_a
+        for (int a = 0; a < D; ++a) V[a] = FO >= 2 ? fma_t(m, U[a], brho * G[a]) : m * U[a];
+        for (int a = 0; a < D; ++a) {
+            K[a] = fma_t(U[a], V[a], e1);
+            for (int b = a + 1; b < D; ++b) Kab[a][b] = fma_t(U[a], V[b], U[b] * V[a]);
         }
-        if constexpr (EQ == 4) K24 = A * T(1.0 / 24.0);
+        if constexpr (EQ == 4) {
+            const T e2 = arho * E2 * T(L::R2 * L::R2);
+            const T d1 = arho * D1 * r2;
+            const T a24 = arho * T(1.0 / 24.0);
+            const T xx = U[0] * U[0], yy = U[1] * U[1], xy = U[0] * U[1];
+            Q[0] = fma_t(xx, fma_t(a24, xx, d1), e2);
+            Q[1] = fma_t(yy, fma_t(a24, yy, d1), e2);
+            Qxy = fma_t(d1, xx + yy, fma_t(T(6) * a24 * xx, yy, T(2) * e2));
+            Qab[0] = xy * fma_t(T(4) * a24, xx, T(2) * d1);
+            Qab[1] = xy * fma_t(T(4) * a24, yy, T(2) * d1);
+        }
+    }
+    // odd coefficients
+    constexpr bool CUBIC = EQ >= 3 || FO >= 3;
+    T O[3], H[3][3], Hxyz = T(0);
+    {
+        T Z[3][3];  // FO >= 3: G_a's quadratic forms, rho xu^2 / 2 - xi.sigma.xi / 2 (times beta)
+        if constexpr (FO == 4) {
+            const T hb2 = T(0.5 * L::R2) * beta;
+            for (int a = 0; a < D; ++a)
+                for (int b = a; b < D; ++b) Z[a][b] = Z[b][a] = -hb2 * cs.sig[a][b];
+            // the linear term of sigma, 2 (beta/2) xi.sigma.g
+            for (int a = 0; a < D; ++a) {
+                T sg = T(0);
+                for (int b = 0; b < D; ++b) sg = fma_t(Z[a][b], G[b], sg);
+                O[a] = T(-2.0 / L::R2) * sg;
+            }
+        }
         if constexpr (FO >= 3) {
-            Kb = Bf * o0;         // odd, times xg
-            Kb2 = Bf * T(0.5);    // odd, times xg xu^2
-        } else {
-            Kb = Bf;
-            Kb2 = T(0);
+            const T hbrho = T(0.5) * brho;
+            for (int a = 0; a < D; ++a) {
+                const T hu = hbrho * U[a];
+                for (int b = a; b < D; ++b)
+                    Z[a][b] = Z[b][a] = FO == 4 ? fma_t(hu, U[b], Z[a][b]) : hu * U[b];
+            }
         }
-        Kbf = Bf;                 // even, times xg xu
-        Kw = hbeta * ws;          // (beta w / 2) for the sigma terms
-    };
+        for (int a = 0; a < D; ++a) {
+            const T au = arho * U[a];
+            const T bg = brho * G[a];
+            // linear
+            T lin;
+            if constexpr (EQ >= 3 && FO >= 3) lin = fma_t(G0, au + bg, -brgu * U[a]);
+            else if constexpr (EQ >= 3) lin = fma_t(G0, au, bg);
+            else if constexpr (FO >= 3) lin = fma_t(G0, bg, fma_t(-brgu, U[a], au));
+            else lin = au + bg;
+            O[a] = FO == 4 ? O[a] + lin : lin;
+            // cubic: c_a c_b^2
+            if constexpr (CUBIC) {
+                const T iso = G1 * r2 * (EQ >= 3 && FO >= 3 ? au + bg : (EQ >= 3 ? au : bg));
+                for (int b = 0; b < D; ++b) {
+                    T v = iso;
+                    if constexpr (EQ >= 3) v = fma_t(T(a == b ? 1.0 / 6.0 : 0.5) * au, U[b] * U[b], v);
+                    if constexpr (FO >= 3) {
+                        v = fma_t(G[a], Z[b][b], v);
+                        if (a != b) v = fma_t(T(2) * G[b], Z[a][b], v);
+                    }
+                    H[a][b] = v;
+                }
+            }
+        }
+        if constexpr (CUBIC && D == 3) {
+            if constexpr (EQ >= 3) Hxyz = arho * U[0] * U[1] * U[2];
+            if constexpr (FO >= 3)
+                Hxyz = fma_t(T(2), fma_t(G[0], Z[1][2], fma_t(G[1], Z[0][2], G[2] * Z[0][1])),
+                             Hxyz);
+        }
+    }
 
     // rest velocity
-    shell_consts(std::integral_constant<int, L::shell(0)>{});
-    cb(std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{}, K0, T(0));
+    constexpr double w0 = L::wshell(L::shell(0)) * SC::template scale<0>();
+    cb(std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{}, T(w0) * C, T(0));
 
-    static_for<0, (L::Q - 1) / 2>([&](auto K) {
-        constexpr int ip = 1 + 2 * decltype(K)::value;
-        constexpr int im = ip + 1;
-        constexpr int s = L::shell(ip);
-        if constexpr (L::shell(ip - 1) != s) shell_consts(std::integral_constant<int, s>{});
-        constexpr int cx = L::c(ip, 0), cy = L::c(ip, 1), cz = L::c(ip, 2);
-        // xi.u and xi.g with compile-time integer components
-        auto dot = [&](const T v[3]) {
-            T acc = T(0);
-            bool first = true;
-            static_for<0, 3>([&](auto A) {
-                constexpr int a = decltype(A)::value;
-                constexpr int ca = (a == 0 ? cx : (a == 1 ? cy : cz));
-                if constexpr (ca != 0) {
-                    if (first) {
-                        acc = (ca == 1) ? v[a] : ((ca == -1) ? -v[a] : T(ca) * v[a]);
-                        first = false;
-                    } else {
-                        if constexpr (ca == 1) acc += v[a];
-                        else if constexpr (ca == -1) acc -= v[a];
-                        else acc += T(ca) * v[a];
-                    }
-                }
-            });
-            return acc;
-        };
-        const T xu = dot(ur);
-        const T xu2 = xu * xu;
-        T ev = K0 + Ka * xu2;
-        if constexpr (EQ == 4) ev += K24 * xu2 * xu2;
-        T od = xu * (Kq + K6 * xu2);
-        if constexpr (FO >= 1) {
-            const T xg = dot(gr);
-            if constexpr (FO >= 2) ev += Kbf * (xg * xu);
-            T gterm = Kb + Kb2 * xu2;
-            if constexpr (FO == 4) {
-                // xi.sigma.xi = r^2 c.sigma.c and xi.sigma.g = r c.(sigma g)
-                T S = T(0);
-                static_for<0, 3>([&](auto A) {
-                    constexpr int a = decltype(A)::value;
-                    constexpr int ca = (a == 0 ? cx : (a == 1 ? cy : cz));
-                    static_for<a, 3>([&](auto B) {
-                        constexpr int b = decltype(B)::value;
-                        constexpr int cb_ = (b == 0 ? cx : (b == 1 ? cy : cz));
-                        constexpr int m = (a == b) ? ca * cb_ : 2 * ca * cb_;
-                        if constexpr (m != 0) S += T(m) * sr[a][b];
+    // orbits on the axes first: they need no mixed coefficient, so the populations
+    // they take are gone before those are formed (two FP64 registers a lane)
+    static_for<0, 3 * L::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value % L::Q, n = decltype(I)::value / L::Q + 1;
+        if constexpr (orbit_rep<L>(i) && Orbit<L>(i).n == n) {
+            constexpr Orbit<L> o(i);
+            constexpr double w = L::wshell(L::shell(i)) * SC::template scale<i>();
+            constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
+            constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
+            // k^2 (K + k^2 Q) of one axis, and the odd part's G + k^2 H
+            auto even1 = [&](auto A, T acc) {
+                constexpr int a = decltype(A)::value, k = L::c(i, a);
+                if constexpr (EQ == 4) return fma_t(T(k * k), fma_t(T(k * k), Q[a], K[a]), acc);
+                else return fma_t(T(k * k), K[a], acc);
+            };
+            auto odd1 = [&](auto A) {
+                constexpr int a = decltype(A)::value, k = L::c(i, a);
+                T v = O[a];
+                if constexpr (CUBIC) {
+                    v = fma_t(T(k * k), H[a][a], v);
+                    static_for<0, D>([&](auto B) {
+                        constexpr int b = decltype(B)::value, kb = L::c(i, b);
+                        if constexpr (b != a && kb != 0) v = fma_t(T(kb * kb), H[a][b], v);
                     });
-                });
-                const T hxi = dot(hr);
-                gterm -= Kw * S;
-                od += T(2) * Kw * hxi;
+                }
+                return T(w * k) * v;
+            };
+            auto cross = [&](auto A, auto B) {
+                constexpr int a = decltype(A)::value, b = decltype(B)::value;
+                constexpr int ka = L::c(i, a), kb = L::c(i, b);
+                T v = Kab[a][b];
+                if constexpr (EQ == 4)
+                    v = fma_t(T(kb * kb), Qab[1], fma_t(T(ka * ka), Qab[0], v));
+                return T(w * ka * kb) * v;
+            };
+            auto emit = [&](auto J, T ev, T od) {
+                constexpr int ip = o.plus(i, decltype(J)::value);
+                constexpr int im = opposite<L>(ip);
+                cb(std::integral_constant<int, ip>{}, std::integral_constant<int, im>{}, ev, od);
+            };
+            using A0 = std::integral_constant<int, a0>;
+            using A1 = std::integral_constant<int, a1>;
+            using A2 = std::integral_constant<int, a2>;
+            T e = even1(A0{}, C);
+            if constexpr (o.n == 1) {
+                emit(std::integral_constant<int, 0>{}, T(w) * e, odd1(A0{}));
+            } else if constexpr (o.n == 2) {
+                e = even1(A1{}, e);
+                if constexpr (EQ == 4) e = fma_t(T(k0 * k0 * k1 * k1), Qxy, e);
+                e *= T(w);
+                const T x = cross(A0{}, A1{});
+                const T p = odd1(A0{}), q = odd1(A1{});
+                emit(std::integral_constant<int, 0>{}, e + x, p + q);
+                emit(std::integral_constant<int, 1>{}, e - x, p - q);
+            } else {
+                e = T(w) * even1(A2{}, even1(A1{}, e));
+                const T x = cross(A0{}, A1{}), y = cross(A0{}, A2{}), z = cross(A1{}, A2{});
+                const T p = odd1(A0{}), q = odd1(A1{}), v = odd1(A2{});
+                const T h = CUBIC ? T(w * k0 * k1 * k2) * Hxyz : T(0);
+                // signs (+, s1, s2): even e + s1 x + s2 y + s1 s2 z, odd p + s1 q + s2 v + s1 s2 h
+                const T ex = e + x, em = e - x, yz = y + z, ym = y - z;
+                const T pq = p + q, pm = p - q, vh = v + h, vm = v - h;
+                emit(std::integral_constant<int, 0>{}, ex + yz, pq + vh);
+                emit(std::integral_constant<int, 1>{}, ex - yz, pq - vh);
+                emit(std::integral_constant<int, 2>{}, em + ym, pm + vm);
+                emit(std::integral_constant<int, 3>{}, em - ym, pm - vm);
             }
-            od += xg * gterm;
         }
-        cb(std::integral_constant<int, ip>{}, std::integral_constant<int, im>{}, ev, od);
     });
 }
 

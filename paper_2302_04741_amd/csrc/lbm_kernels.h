@@ -135,8 +135,8 @@ __device__ __forceinline__ double wall_emitted(const WallDesc &wd, const GridDim
                                                double w, double rho0, int x, int y, int z)
 {
     const int side = y - L::c(i, 1) < 0 ? 0 : 1;
-    const int xv = wrap3(x - L::c(i, 0), gd.nx);
-    const int zv = (L::D == 3) ? wrap3(z - L::c(i, 2), gd.nz) : 0;
+    const int xv = int(wrap_back(uint32_t(x), L::c(i, 0), uint32_t(gd.nx)));
+    const int zv = (L::D == 3) ? int(wrap_back(uint32_t(z), L::c(i, 2), uint32_t(gd.nz))) : 0;
     const int64_t ncol = int64_t(gd.nx) * gd.nz;
     const int64_t col = int64_t(zv) * gd.nx + xv;
     // the plate's density over the source column: its rows' sums, in order
@@ -152,18 +152,19 @@ __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &
                                        int z, T (&h)[L::Q], const WallDesc *wd = nullptr,
                                        double rho0 = 0.0)
 {
-    // x offsets are per lane (7 distinct byte offsets); y and z are uniform over
-    // the wavefront, so each row offset and each plane resource is a scalar.
-    uint32_t xs[7];
-    int ys[7], zs[7];
+    // Byte offsets: 7 per lane along x; y and z are uniform over the wavefront, so
+    // each row offset and each plane resource is a scalar.  A plane is < 4 GiB
+    // (checked at creation), so are all of them.
+    const uint32_t pitch = uint32_t(gd.px) * uint32_t(sizeof(S));
+    const uint32_t slab = pitch * uint32_t(gd.ny);
+    uint32_t xs[7], ys[7], zs[7];
 #pragma unroll
-    for (int d = 0; d < 7; ++d) {
-        xs[d] = uint32_t(wrap3(x - (d - 3), gd.nx)) * uint32_t(sizeof(S));
-        ys[d] = wrap3(y - (d - 3), gd.ny);
-        zs[d] = (L::D == 3) ? wrap3(z - (d - 3), gd.nz) : 0;
+    for (int d = -3; d <= 3; ++d) {
+        xs[d + 3] = wrap_back(uint32_t(x), d, uint32_t(gd.nx)) * uint32_t(sizeof(S));
+        ys[d + 3] = wrap_back(uint32_t(y), d, uint32_t(gd.ny)) * pitch;
+        zs[d + 3] = (L::D == 3) ? wrap_back(uint32_t(z), d, uint32_t(gd.nz)) * slab : 0u;
     }
-    const int64_t P = gd.P;
-    const uint32_t plane_bytes = uint32_t(P * int64_t(sizeof(S)));
+    PlaneWalk planes(A, uint32_t(gd.P * int64_t(sizeof(S))));
     static_for<0, L::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c(i, 0), cy = L::c(i, 1), cz = L::c(i, 2);
@@ -176,10 +177,8 @@ __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &
                 return;
             }
         }
-        const uint32_t row =
-            uint32_t((int64_t(zs[cz + 3]) * gd.ny + ys[cy + 3]) * gd.px) * uint32_t(sizeof(S));
-        const auto r = plane_rsrc(A + int64_t(i) * P, plane_bytes);
-        h[i] = Codec<L, S>::template load_scaled<i, T>(BufIO<S>::load(r, xs[cx + 3], row));
+        h[i] = Codec<L, S>::template load_scaled<i, T>(
+            BufIO<S>::load(planes.at(i), xs[cx + 3], zs[cz + 3] + ys[cy + 3]));
     });
 }
 
@@ -193,21 +192,47 @@ template <class S> constexpr int step_max_threads()
     return sizeof(typename ArithOf<S>::type) == 8 ? 256 : 1024;
 }
 
-// Default block of the step, measured: 4 wavefronts, except 16 for D3Q39 FP32
-// storage on grids of at least 2^17 wavefronts (256^3: +2%, 384^3: +2%; on
-// smaller D3Q39 grids and on every D2Q37 grid 16-wavefront blocks lose 5-20%,
-// F16 storage loses 5% with them) and 2 for FP64 storage (D3Q39 256^3: +6%,
-// D2Q37 1024^2: +4% over 4; FP64 cannot use more than 4).
-template <int LAT, class S> inline int step_default_threads(int64_t waves)
+// Launch shape of the step: threads per block, and the LDS bytes a block asks for
+// (unused: they only limit how many blocks share a CU).
+struct StepShape {
+    int threads;
+    unsigned lds;
+};
+
+// Default, measured.  FP64: 128 threads (D3Q39 256^3: +6%, D2Q37 1024^2: +4% over
+// 256, which is its largest).  FP32 and F16: 256, except FP32 populations past the
+// 256 MB memory-side cache by far (a buffer of 400 MB and more): there the rate
+// falls with the wavefronts in flight, whose loads and stores open ever more
+// places of the 78 plane streams at once, and the arithmetic needs few of them,
+// so a CU gets 8 wavefronts, one block of 512 threads.  FP32 us a step, 8
+// wavefronts against as many as the registers allow (256 threads): D3Q39 160^3
+// 227 / 234, 224^3 614 / 657, 256^3 913 / 957 (1024 threads, 16 wavefronts: 942),
+// D2Q37 2048^2 220 / 226, 3000^2 475 / 500; below that size it gains or loses 2%,
+// and F16, with half the bytes a wavefront, loses (256^3 700 / 496).
+constexpr int64_t STEP_LARGE_BYTES = int64_t(400) << 20;
+constexpr unsigned STEP_LDS_PER_CU = 160u << 10;
+
+template <class S> inline StepShape step_shape(int64_t buffer_bytes, int threads)
 {
-    if (sizeof(S) == 8) return 128;
-    return (LAT == 1 && sizeof(S) == 4 && waves >= (int64_t(1) << 17)) ? 1024 : 256;
+    const bool large = sizeof(S) == 4 && buffer_bytes >= STEP_LARGE_BYTES;
+    int bx = threads > 0 ? threads : (sizeof(S) == 8 ? 128 : (large ? 512 : 256));
+    bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
+    const bool limit = large && (bx == 256 || bx == 512);
+    return StepShape{bx, limit ? STEP_LDS_PER_CU * unsigned(bx) / 512u : 0u};
 }
 
 // The fused update of one cell (x, y, z): gather, moments, equilibrium, stress,
 // force, relaxation, store.  y and z must be uniform over the wavefront.
 // `step` is the step number (the state read is after `step` steps): with F16
 // storage it keys the stochastic rounding of every value stored.
+//
+// Bound by memory on large grids and by the length of its instruction stream on
+// small ones (one wavefront a SIMD or fewer: each instruction is latency).  The
+// stream is 925 instructions for D2Q37 FP32 (523 vector, 324 scalar) and 1051 for
+// D3Q39 FP32 (579, 388); with the pair-by-pair evaluation, looping wraps and a
+// resource made for each access it was 1860 and 2211.  Step of D2Q37 64^2 FP64:
+// 5.7 -> 4.7 us, of the plated 3 x 150 channel 15.3 -> 12.2 us, of D2Q37 256^2 FP32
+// 8.4 -> 7.9 us; at 1024^2 and above the memory time hid most of it already.
 template <int LAT, class S, int EQ, int FO, bool WALLS = false>
 __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict__ B,
                                           const GridDims &gd, const ForceDesc &fd,
@@ -216,12 +241,9 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
 {
     using L = Lattice<LAT>;
     using T = typename ArithOf<S>::type;
-    const int64_t P = gd.P;
     const int64_t row = int64_t(z) * gd.ny + y;  // uniform
     const int64_t rowbase = row * gd.px;          // padded population row
     const int64_t cell = row * gd.nx + x;         // dense field index
-    // one population plane is < 4 GiB (checked at creation), so 32-bit byte
-    // offsets address it
 
     // h holds the deviations as stored, times Codec::scale<i>() (1 unless the
     // storage is reduced-precision); the sums and the pair terms take the
@@ -237,22 +259,16 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
     CellState<T> cs;
     finish_moments<L, T, FO == 4>(rs, g, co, cs);
 
-    // h* = h + om (f0 - f) + cf F with f0 - f = w drho + (f0 - w rho) - h.
-    // The bracket [om (f0 - w rho) + cf F] is what combo_pairs returns with
-    // NO_BASE (even +- odd part).  FP32 arithmetic: h* = (1 - om) h + [om w
-    // drho + bracket], a pair sharing q = fma(om w, drho, even), each
-    // population one fma(1 - om, h, q +- odd) (1 - om is exact: om = 1/tau^
-    // lies in [1/2, 2]).  FP64 arithmetic keeps h + fma(om, fma(w, drho, -h),
-    // even +- odd), which needs one register less per lane (the other form
-    // takes its D3Q39 step from three wavefronts per SIMD to two).  Either way
-    // every term is a small deviation, so the rounding stays at the size of h.
-    constexpr bool SHARED_Q = sizeof(T) == 4;
+    // h* = h + om (f0 - f) + cf F with f0 - f = w drho + (f0 - w rho) - h, so
+    // h* = (1 - om) h + [om w drho + om (f0 - w rho) + cf F]; the bracket is what
+    // combo_pairs returns with NO_BASE and base = om drho (even +- odd part), each
+    // population one fma of it (1 - om is exact for om = 1/tau^ in [1/2, 2]).
+    // Every term is a small deviation, so the rounding stays at the size of h.
     const T om = cs.om;
     const T omc = T(1) - om;
-    const T drho = cs.drho;
     const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
     const uint32_t ro = uint32_t(rowbase) * uint32_t(sizeof(S));
-    const uint32_t plane_bytes = uint32_t(P * int64_t(sizeof(S)));
+    PlaneWalk planes(B, uint32_t(gd.P * int64_t(sizeof(S))));
     // with plates: the partial sums of the state written here (the slots whose
     // next move crosses a plate, as stored), for the next step's emission
     double ps[2] = {0.0, 0.0};
@@ -268,22 +284,17 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
             }
         }
     };
-    combo_pairs<L, T, EQ, FO, true, C>(cs, om, cs.cf, [&](auto IP, auto IM, T ev, T od) {
+    combo_pairs<L, T, EQ, FO, true, C>(cs, om, cs.cf, om * cs.drho,
+                                       [&](auto IP, auto IM, T ev, T od) {
         constexpr int ip = decltype(IP)::value;
         constexpr int im = decltype(IM)::value;
-        constexpr double w = L::wshell(L::shell(ip)) * C::template scale<ip>();
-        T q = T(0);
-        if constexpr (SHARED_Q) q = fma_t(om * T(w), drho, ev);
-        auto relaxed = [&](T hi, T sign_od) {
-            if constexpr (SHARED_Q) return fma_t(omc, hi, q + sign_od);
-            else return hi + fma_t(om, fma_t(T(w), drho, -hi), ev + sign_od);
-        };
+        auto relaxed = [&](T hi, T sign_od) { return fma_t(omc, hi, ev + sign_od); };
         const S sp = C::template store_scaled<ip, T>(relaxed(h[ip], od), rng);
-        BufIO<S>::store(sp, plane_rsrc(B + int64_t(ip) * P, plane_bytes), xo, ro);
+        BufIO<S>::store(sp, planes.at(ip), xo, ro);
         account(IP, sp);
         if constexpr (im >= 0) {
             const S sm = C::template store_scaled<im, T>(relaxed(h[im], -od), rng);
-            BufIO<S>::store(sm, plane_rsrc(B + int64_t(im) * P, plane_bytes), xo, ro);
+            BufIO<S>::store(sm, planes.at(im), xo, ro);
             account(IM, sm);
         }
     });
@@ -332,12 +343,10 @@ __device__ __forceinline__ bool wave_cell(const GridDims &gd, uint32_t wave, int
     return x < gd.nx;
 }
 
-// Wavefronts per SIMD the compiler must leave room for (registers at most
-// 512 / 5 rounded down to the allocation granule): FP32 arithmetic fits five
-// without spills; left free, the F16 step's stochastic rounding led the
-// scheduler to a four-wave schedule (101 registers) that ran slower.  FP64
-// arithmetic needs more than 128 registers and is not constrained.
-template <class S> constexpr int step_min_waves() { return sizeof(S) == 8 ? 1 : 5; }
+// Wavefronts per SIMD the compiler must leave room for: FP32 arithmetic fits
+// five without spills; FP64 needs three (168 registers; left free, the D3Q39
+// schedule takes 170).
+template <class S> constexpr int step_min_waves() { return sizeof(S) == 8 ? 3 : 5; }
 
 template <int LAT, class S, int EQ, int FO>
 __global__ void __launch_bounds__(step_max_threads<S>())
@@ -371,10 +380,10 @@ __global__ void __launch_bounds__(step_max_threads<S>())
     gather<L, S, S>(A, gd, x, y, z, h);
     const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
     const uint32_t ro = uint32_t((int64_t(z) * gd.ny + y) * gd.px) * uint32_t(sizeof(S));
-    const uint32_t plane_bytes = uint32_t(gd.P * int64_t(sizeof(S)));
+    PlaneWalk planes(B, uint32_t(gd.P * int64_t(sizeof(S))));
     static_for<0, L::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        BufIO<S>::store(h[i], plane_rsrc(B + int64_t(i) * gd.P, plane_bytes), xo, ro);
+        BufIO<S>::store(h[i], planes.at(i), xo, ro);
     });
 }
 
@@ -508,10 +517,10 @@ __global__ void __launch_bounds__(256)
     }
     constexpr int FOI = FO == 4 ? 3 : FO;  // sigma = 0 at the start
     // h = w (rho - rho0) + (f0 - w rho) - F/2
-    combo_pairs<L, T, EQ, FOI, true>(cs, T(1), T(-0.5), [&](auto IP, auto IM, T ev, T od) {
+    combo_pairs<L, T, EQ, FOI, true>(cs, T(1), T(-0.5), cs.drho,
+                                     [&](auto IP, auto IM, T ev, T od) {
         constexpr int ip = decltype(IP)::value;
         constexpr int im = decltype(IM)::value;
-        constexpr double w = L::wshell(L::shell(ip));
         auto put = [&](auto II, T v) {
             constexpr int i = decltype(II)::value;
             const S sv = Codec<L, S>::template store<i, T>(v);
@@ -525,15 +534,15 @@ __global__ void __launch_bounds__(256)
                 }
                 if (y - L::c(i, 1) < 0 || y - L::c(i, 1) >= gd.ny) return;
             }
-            const int xd = wrap3(x - L::c(i, 0), gd.nx);
-            const int yd = wrap3(y - L::c(i, 1), gd.ny);
-            const int zd = (L::D == 3) ? wrap3(z - L::c(i, 2), gd.nz) : 0;
+            const int xd = int(wrap_back(uint32_t(x), L::c(i, 0), uint32_t(gd.nx)));
+            const int yd = int(wrap_back(uint32_t(y), L::c(i, 1), uint32_t(gd.ny)));
+            const int zd =
+                (L::D == 3) ? int(wrap_back(uint32_t(z), L::c(i, 2), uint32_t(gd.nz))) : 0;
             const int64_t dst = (int64_t(zd) * gd.ny + yd) * gd.px + xd;
             A[int64_t(i) * gd.P + dst] = sv;
         };
-        const T base = T(w) * cs.drho;
-        put(std::integral_constant<int, ip>{}, base + (ev + od));
-        if constexpr (im >= 0) put(std::integral_constant<int, im>{}, base + (ev - od));
+        put(std::integral_constant<int, ip>{}, ev + od);
+        if constexpr (im >= 0) put(std::integral_constant<int, im>{}, ev - od);
     });
 }
 
@@ -613,18 +622,18 @@ __global__ void __launch_bounds__(256)
         }
         for (int a = 0; a < L::D; ++a) qa[a] += d * cc * cv[a];
     };
-    combo_pairs<L, T, EQ, FO, true>(cs, -cf, T(0.5) * cf, [&](auto IP, auto IM, T ev, T od) {
+    combo_pairs<L, T, EQ, FO, true>(cs, -cf, T(0.5) * cf, -cf * cs.drho,
+                                    [&](auto IP, auto IM, T ev, T od) {
         constexpr int ip = decltype(IP)::value;
         constexpr int im = decltype(IM)::value;
-        constexpr double w = L::wshell(L::shell(ip));
-        acc(IP, cf * (h[ip] - T(w) * cs.drho) + (ev + od));
-        if constexpr (im >= 0) acc(IM, cf * (h[im] - T(w) * cs.drho) + (ev - od));
+        acc(IP, fma_t(cf, h[ip], ev + od));
+        if constexpr (im >= 0) acc(IM, fma_t(cf, h[im], ev - od));
     });
     if constexpr (EQ == 2) {
         T u2 = T(0);
         for (int a = 0; a < L::D; ++a) u2 += cs.ub[a] * cs.ub[a];
         for (int a = 0; a < L::D; ++a) qa[a] -= cs.rho * cs.ub[a] * (T(L::D + 2) + u2);
-        combo_pairs<L, T, 2, 1, true>(cs, T(1), T(0), [&](auto IP, auto IM, T ev, T od) {
+        combo_pairs<L, T, 2, 1, true>(cs, T(1), T(0), T(0), [&](auto IP, auto IM, T ev, T od) {
             acc(IP, ev + od);
             if constexpr (decltype(IM)::value >= 0) acc(IM, ev - od);
         });
@@ -664,8 +673,8 @@ __global__ void __launch_bounds__(64)
         cs.cf = 0.0;
         double *es = e + side * (L::Q + 1);
         // f0 = w rho + (f0 - w rho); the bracket is combo_pairs' NO_BASE part
-        combo_pairs<L, double, EQ, 1, true>(cs, 1.0, 0.0, [&](auto IP, auto IM, double ev,
-                                                            double od) {
+        combo_pairs<L, double, EQ, 1, true>(cs, 1.0, 0.0, 0.0, [&](auto IP, auto IM, double ev,
+                                                                 double od) {
             constexpr int ip = decltype(IP)::value;
             constexpr int im = decltype(IM)::value;
             constexpr double w = L::wshell(L::shell(ip));

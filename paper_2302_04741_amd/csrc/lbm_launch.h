@@ -39,13 +39,13 @@ hipError_t launch_step_ls(int eq, int fo, const void *A, void *B, const GridDims
 {
     // blocks of bx/64 wavefronts, one wavefront per 64 cells of a row
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    int bx = lc.block > 0 ? lc.block : step_default_threads<LAT, S>(waves);
-    bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
-    const int64_t wpb = bx / 64;
+    const StepShape sh =
+        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         hipLaunchKernelGGL((step_kernel<LAT, S, decltype(E)::value, decltype(O)::value>), grid,
-                           dim3(bx), 0, lc.stream, static_cast<const S *>(A),
+                           dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A),
                            static_cast<S *>(B), gd, fd, co, lc.ctr, lc.cur);
         return hipGetLastError();
     });
@@ -56,11 +56,11 @@ hipError_t launch_pattern_ls(const void *A, void *B, const GridDims &gd, const L
 {
     // the launch shape of the step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    int bx = lc.block > 0 ? lc.block : step_default_threads<LAT, S>(waves);
-    bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
-    const int64_t wpb = bx / 64;
+    const StepShape sh =
+        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t wpb = sh.threads / 64;
     hipLaunchKernelGGL((pattern_kernel<LAT, S>), dim3(unsigned((waves + wpb - 1) / wpb)),
-                       dim3(bx), 0, lc.stream, static_cast<const S *>(A), static_cast<S *>(B),
+                       dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A), static_cast<S *>(B),
                        gd);
     return hipGetLastError();
 }
@@ -133,13 +133,13 @@ hipError_t launch_wall_step_ls(int eq, int fo, const void *A, void *B, const Gri
 {
     // the work split of the periodic step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    int bx = lc.block > 0 ? lc.block : step_default_threads<LAT, S>(waves);
-    bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
-    const int64_t wpb = bx / 64;
+    const StepShape sh =
+        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         hipLaunchKernelGGL((wall_step_kernel<LAT, S, decltype(E)::value, decltype(O)::value>),
-                           grid, dim3(bx), 0, lc.stream, static_cast<const S *>(A),
+                           grid, dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A),
                            static_cast<S *>(B), gd, fd, co, lc.walls, lc.ctr, lc.cur);
         return hipGetLastError();
     });

@@ -70,3 +70,52 @@ def test_division_constants_exact(tmp_path):
     run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0, run.stdout[-2000:]
     assert "all exact" in run.stdout
+
+
+WRAP_PROGRAM = r"""
+#include <stdio.h>
+#include <stdint.h>
+#include "fastdiv.h"
+
+static int check(uint32_t v, int d, uint32_t n)
+{
+    const int64_t want = ((int64_t(v) - d) % int64_t(n) + int64_t(n)) % int64_t(n);
+    const uint32_t got = lbm::wrap_back(v, d, n);
+    if (int64_t(got) == want) return 0;
+    printf("mismatch v=%u d=%d n=%u: %u vs %lld\n", v, d, n, got, (long long)want);
+    return 1;
+}
+
+int main(void)
+{
+    int bad = 0;
+    for (uint32_t n = 1; n <= 300u; ++n)
+        for (uint32_t v = 0; v < n; ++v)
+            for (int d = -3; d <= 3; ++d) bad |= check(v, d, n);
+    for (int k = 9; k <= 31; ++k)
+        for (int e = -2; e <= 2; ++e) {
+            const uint32_t n = (1u << k) + uint32_t(k < 31 || e < 0 ? e : 0);
+            for (uint32_t o = 0; o < 8u; ++o)
+                for (int d = -3; d <= 3; ++d)
+                    bad |= check(o, d, n) | check(n - 1u - o, d, n) | check(n / 2u + o, d, n);
+        }
+    puts(bad ? "wrap: mismatches" : "wrap: all exact");
+    return bad;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_periodic_wrap_exact(tmp_path):
+    """wrap_back(v, d, n) == (v - d) mod n for |d| <= 3: every v of n = 1..300 (n < 4
+    takes the shift modulo n), and both ends of the row up to n = 2^31."""
+    src = tmp_path / "wrap_check.cpp"
+    src.write_text(WRAP_PROGRAM)
+    exe = tmp_path / "wrap_check"
+    cmd = ["g++", "-std=c++17", "-O2", "-D__host__=", "-D__device__=", "-I" + CSRC, str(src),
+           "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stdout[-2000:]
+    assert "all exact" in run.stdout
