@@ -675,12 +675,13 @@ void fill_tile_sim(TileSim &t, const lbm_sim *s, int64_t first_tile)
 
 // Write the tile table of `sims` (64-cell tiles) to begin[count + 1] and
 // tab[count] on `stream`; tiles = the length of the list, walls = some member
-// has plates.
+// has plates, bytes = one population buffer of every member, in whole lines.
 hipError_t upload_table(lbm_sim *const *sims, int32_t count, int64_t *begin, TileSim *tab,
-                        hipStream_t stream, int64_t &tiles, bool &walls)
+                        hipStream_t stream, int64_t &tiles, bool &walls, int64_t &bytes)
 {
     tiles = 0;
     walls = false;
+    bytes = 0;
     for (int32_t first = 0; first < count; first += TABLE_CHUNK) {
         TableChunk c;
         std::memset(&c, 0, sizeof c);
@@ -692,6 +693,8 @@ hipError_t upload_table(lbm_sim *const *sims, int32_t count, int64_t *begin, Til
             c.begin[k] = tiles;
             tiles += int64_t(c.sims[k].chunks_x) * s->p.ny * s->p.nz;
             walls = walls || s->wd.on;
+            const int64_t row = s->p.nx * int64_t(storage_bytes(s->p.storage));
+            bytes += int64_t(s->Q) * s->p.ny * s->p.nz * ((row + 127) / 128 * 128);
         }
         c.last = first + c.n == count;
         c.end = tiles;
@@ -718,6 +721,7 @@ struct lbm_batch {
     int threads;     // threads per block (tiles of 64 cells, one per wavefront)
     int64_t blocks;  // 0: one block per tile
     bool walls;           // some member has plates
+    int64_t bytes;        // one population buffer of every member together, whole lines
 };
 
 struct lbm_graph {
@@ -769,7 +773,7 @@ lbm_status batch_launch(lbm_batch *b, int64_t nsteps, int64_t &done)
     for (done = 0; done < nsteps; ++done) {
         const int parity = int((b->steps_done + done) & 1);
         const BatchLaunch bl{b->begin,  b->table,   int(b->sims.size()), b->ntiles, parity,
-                             b->threads, b->blocks, b->stream,           b->walls};
+                             b->threads, b->blocks, b->stream,           b->walls,  b->bytes};
         hipError_t e = launch_multi_step(s0->p.lattice, s0->p.storage, s0->eq, s0->p.force_order,
                                          bl);
         if (e != hipSuccess) return dev_fail(e, "multi-grid step launch");
@@ -785,7 +789,8 @@ lbm_status batch_build(lbm_batch *b, lbm_sim *const *sims, int32_t count)
     if (st != LBM_OK) return st;
     int64_t tiles = 0;
     bool walls = false;
-    hipError_t e = upload_table(sims, count, b->begin, b->table, b->stream, tiles, walls);
+    int64_t bytes = 0;
+    hipError_t e = upload_table(sims, count, b->begin, b->table, b->stream, tiles, walls, bytes);
     if (e != hipSuccess) return dev_fail(e, "tile table fill launch");
     b->sims.assign(sims, sims + count);
     b->step_at_set.clear();
@@ -798,6 +803,7 @@ lbm_status batch_build(lbm_batch *b, lbm_sim *const *sims, int32_t count)
     b->generation++;
     b->ntiles = tiles;
     b->walls = walls;
+    b->bytes = bytes;
     return LBM_OK;
 }
 
@@ -845,6 +851,7 @@ lbm_status lbm_batch_create(int32_t max_sims, void *workspace, size_t workspace_
     b->threads = BATCH_DEFAULT_THREADS;
     b->blocks = 0;
     b->walls = false;
+    b->bytes = 0;
     *out = b;
     return ok();
 }
@@ -967,13 +974,14 @@ lbm_status lbm_batch_step_noalloc(lbm_sim *const *sims, int32_t count, int64_t n
     TileSim *table = reinterpret_cast<TileSim *>(base + NOALLOC_BEGIN_BYTES);
     int64_t tiles = 0;
     bool walls = false;
-    e = upload_table(sims, count, begin, table, stream, tiles, walls);
+    int64_t bytes = 0;
+    e = upload_table(sims, count, begin, table, stream, tiles, walls, bytes);
     if (e != hipSuccess) return dev_fail(e, "tile table fill launch");
     const lbm_sim *s0 = sims[0];
     int64_t done = 0;
     for (; done < nsteps; ++done) {
         const BatchLaunch bl{begin,  table, int(count), tiles, int(done & 1), BATCH_DEFAULT_THREADS,
-                             0,      stream, walls};
+                             0,      stream, walls, bytes};
         e = launch_multi_step(s0->p.lattice, s0->p.storage, s0->eq, s0->p.force_order, bl);
         if (e != hipSuccess) break;
     }

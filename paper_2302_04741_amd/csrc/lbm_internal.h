@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "fastdiv.h"
 #include "lattice_tables.h"
@@ -28,13 +29,15 @@ namespace lbm {
 // ---------------------------------------------------------------------------
 // compile-time loops
 // ---------------------------------------------------------------------------
-template <int I, int N, typename F>
-__host__ __device__ __forceinline__ void static_for(F &&f)
+template <int I, typename F, int... K>
+__host__ __device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, K...>)
 {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(static_cast<F &&>(f));
-    }
+    (f(std::integral_constant<int, I + K>{}), ...);
+}
+template <int I, int N, typename F> __host__ __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N)
+        static_for_seq<I>(static_cast<F &&>(f), std::make_integer_sequence<int, N - I>{});
 }
 
 // fused multiply-add in the precision of its arguments
@@ -47,12 +50,42 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return _
 // and the hardware range check drops accesses past the plane.
 // ---------------------------------------------------------------------------
 constexpr int BUF_DWORD3 = 0x00020000;  // raw buffer, 32-bit data format
-// Cache policy of the step's population traffic.  Every element is read once
-// and written once per step.  Stores are non-temporal (6% faster than default
-// stores on the D3Q39 FP32 step); loads keep the default policy (1.3% / 1.8% /
-// 4.5% faster than non-temporal loads for FP32 / FP64 / F16 storage).
-constexpr int BUF_LD = 0;
-constexpr int BUF_NT = 2;
+// Cache bits of a buffer access (gfx940 and later): 1 sc0, 2 nt, 16 sc1.  Stores
+// with sc0 sc1 are written through the L2 to the memory side; with nt they are
+// streamed (the memory-side cache does not keep them).
+constexpr int BUF_DEFAULT = 0, BUF_NT = 2, BUF_THROUGH = 17, BUF_STREAM = 18;
+
+// Cache policy of the step's population traffic: every element is read once and
+// written once a step, and what one step writes is what the next one reads, so
+// the 256 MB memory-side cache can serve part of a step's reads where the stores
+// leave their lines in it.  T: bytes of one population buffer, whole 128-byte
+// lines.  us a step, by policy (FP32 unless noted):
+//                            RESIDENT  KEEP_WRITES  STREAM   (nt stores alone)
+//   D2Q37 512^2    T 39 MB     14.8       18.2       18.2       18.2
+//   D2Q37 900^2    T 124 MB    38.7       47.6       46.5       46.4
+//   D3Q39 96^3 F16 T 71 MB     26.4       40.7       41.1       39.7
+//   D3Q39 96^3     T 138 MB    51.5       45.7       53         55.1
+//   D3Q39 128^3    T 327 MB   127        110.6      122        127.6
+//   D2Q37 1024^2 FP64 310 MB  128        105.5      117        125.3
+//   D3Q39 144^3    T 466 MB                         181.9      186.9
+//   D3Q39 256^3 FP64 5.2 GB  1902       1886       1825       1889
+// RESIDENT: both buffers fit: default loads, stores written through (written back
+// by default they cost the same, but leave the L2's dirty lines to the end of the
+// launch).  KEEP_WRITES: one buffer fits about: loads marked nt leave the cache
+// to what is being written.  STREAM: neither: stores streamed.
+// Reversed: odd steps sweep the grid backwards, so that a step first reads what
+// the last one wrote last; it pays once T exceeds half the cache.
+enum class Policy { RESIDENT, KEEP_WRITES, STREAM };
+template <Policy P> struct CacheBits;
+template <> struct CacheBits<Policy::RESIDENT> {
+    static constexpr int load = BUF_DEFAULT, store = BUF_THROUGH;
+};
+template <> struct CacheBits<Policy::KEEP_WRITES> {
+    static constexpr int load = BUF_NT, store = BUF_THROUGH;
+};
+template <> struct CacheBits<Policy::STREAM> {
+    static constexpr int load = BUF_DEFAULT, store = BUF_STREAM;
+};
 
 typedef int RsrcWords __attribute__((ext_vector_type(4)));
 typedef int Words2 __attribute__((ext_vector_type(2)));
@@ -90,33 +123,39 @@ struct PlaneWalk {
 
 template <class S> struct BufIO;
 template <> struct BufIO<float> {
+    template <int LD>
     __device__ static __forceinline__ float load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return buf_load_f32(r, int(v), int(s), BUF_LD);
+        return buf_load_f32(r, int(v), int(s), LD);
     }
+    template <int ST>
     __device__ static __forceinline__ void store(float x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        buf_store_f32(x, r, int(v), int(s), BUF_NT);
+        buf_store_f32(x, r, int(v), int(s), ST);
     }
 };
 template <> struct BufIO<double> {
+    template <int LD>
     __device__ static __forceinline__ double load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return __builtin_bit_cast(double, buf_load_2i32(r, int(v), int(s), BUF_LD));
+        return __builtin_bit_cast(double, buf_load_2i32(r, int(v), int(s), LD));
     }
+    template <int ST>
     __device__ static __forceinline__ void store(double x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        buf_store_2i32(__builtin_bit_cast(Words2, x), r, int(v), int(s), BUF_NT);
+        buf_store_2i32(__builtin_bit_cast(Words2, x), r, int(v), int(s), ST);
     }
 };
 template <> struct BufIO<__half> {
+    template <int LD>
     __device__ static __forceinline__ __half load(RsrcWords r, uint32_t v, uint32_t s)
     {
-        return __builtin_bit_cast(__half, buf_load_i16(r, int(v), int(s), BUF_LD));
+        return __builtin_bit_cast(__half, buf_load_i16(r, int(v), int(s), LD));
     }
+    template <int ST>
     __device__ static __forceinline__ void store(__half x, RsrcWords r, uint32_t v, uint32_t s)
     {
-        buf_store_i16(__builtin_bit_cast(short, x), r, int(v), int(s), BUF_NT);
+        buf_store_i16(__builtin_bit_cast(short, x), r, int(v), int(s), ST);
     }
 };
 
@@ -184,6 +223,19 @@ template <class L> struct Orbit {
         return velocity_of<L>(c[0], c[1], c[2]);
     }
 };
+
+// The orbits' representatives, those on the axes first, then by nonzero components
+// and plane.
+template <class L> struct OrbitList {
+    int n, rep[L::Q];
+    constexpr OrbitList() : n(0), rep{}
+    {
+        for (int k = 1; k <= 3; ++k)
+            for (int i = 1; i < L::Q; ++i)
+                if (orbit_rep<L>(i) && Orbit<L>(i).n == k) rep[n++] = i;
+    }
+};
+template <class L> constexpr OrbitList<L> ORBITS{};
 
 // ---------------------------------------------------------------------------
 // storage conversion
@@ -366,48 +418,46 @@ __device__ __forceinline__ RawSums<T> raw_sums(const T (&h)[L::Q])
         if (m == 1.0) acc += v;
         else acc = fma_t(v, T(m), acc);
     };
-    static_for<1, L::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        if constexpr (orbit_rep<L>(i)) {
-            constexpr Orbit<L> o(i);
-            constexpr double u = 1.0 / SC::template scale<i>();  // exact: a power of two
-            constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
-            constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
-            T sp[4], dm[4];
-            static_for<0, o.pairs()>([&](auto J) {
-                constexpr int j = decltype(J)::value;
-                constexpr int ip = o.plus(i, j);
-                constexpr int im = opposite<L>(ip);
-                sp[j] = h[ip] + h[im];
-                dm[j] = h[ip] - h[im];
-            });
-            T S;
-            if constexpr (o.n == 1) {
-                S = sp[0];
-                add(s.j[a0], u * k0, dm[0]);
-            } else if constexpr (o.n == 2) {
-                S = sp[0] + sp[1];
-                add(s.P[a0][a1], u * (k0 * k1), sp[0] - sp[1]);
-                add(s.j[a0], u * k0, dm[0] + dm[1]);
-                add(s.j[a1], u * k1, dm[0] - dm[1]);
-            } else {
-                const T pa = sp[0] + sp[1], ma = sp[0] - sp[1];
-                const T pb = sp[2] + sp[3], mb = sp[2] - sp[3];
-                S = pa + pb;
-                add(s.P[a0][a2], u * (k0 * k2), ma + mb);
-                add(s.P[a0][a1], u * (k0 * k1), pa - pb);
-                add(s.P[a1][a2], u * (k1 * k2), ma - mb);
-                const T qa = dm[0] + dm[1], na = dm[0] - dm[1];
-                const T qb = dm[2] + dm[3], nb = dm[2] - dm[3];
-                add(s.j[a0], u * k0, qa + qb);
-                add(s.j[a2], u * k2, na + nb);
-                add(s.j[a1], u * k1, qa - qb);
-            }
-            add(by_k[a0][k0 - 1], u, S);
-            if constexpr (o.n >= 2) add(by_k[a1][k1 - 1], u, S);
-            if constexpr (o.n >= 3) add(by_k[a2][k2 - 1], u, S);
-            if constexpr (L::c(i, 0) == 0) add(rest, u, S);
+    static_for<0, ORBITS<L>.n>([&](auto I) {
+        constexpr int i = ORBITS<L>.rep[decltype(I)::value];
+        constexpr Orbit<L> o(i);
+        constexpr double u = 1.0 / SC::template scale<i>();  // exact: a power of two
+        constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
+        constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
+        T sp[4], dm[4];
+        static_for<0, o.pairs()>([&](auto J) {
+            constexpr int j = decltype(J)::value;
+            constexpr int ip = o.plus(i, j);
+            constexpr int im = opposite<L>(ip);
+            sp[j] = h[ip] + h[im];
+            dm[j] = h[ip] - h[im];
+        });
+        T S;
+        if constexpr (o.n == 1) {
+            S = sp[0];
+            add(s.j[a0], u * k0, dm[0]);
+        } else if constexpr (o.n == 2) {
+            S = sp[0] + sp[1];
+            add(s.P[a0][a1], u * (k0 * k1), sp[0] - sp[1]);
+            add(s.j[a0], u * k0, dm[0] + dm[1]);
+            add(s.j[a1], u * k1, dm[0] - dm[1]);
+        } else {
+            const T pa = sp[0] + sp[1], ma = sp[0] - sp[1];
+            const T pb = sp[2] + sp[3], mb = sp[2] - sp[3];
+            S = pa + pb;
+            add(s.P[a0][a2], u * (k0 * k2), ma + mb);
+            add(s.P[a0][a1], u * (k0 * k1), pa - pb);
+            add(s.P[a1][a2], u * (k1 * k2), ma - mb);
+            const T qa = dm[0] + dm[1], na = dm[0] - dm[1];
+            const T qb = dm[2] + dm[3], nb = dm[2] - dm[3];
+            add(s.j[a0], u * k0, qa + qb);
+            add(s.j[a2], u * k2, na + nb);
+            add(s.j[a1], u * k1, qa - qb);
         }
+        add(by_k[a0][k0 - 1], u, S);
+        if constexpr (o.n >= 2) add(by_k[a1][k1 - 1], u, S);
+        if constexpr (o.n >= 3) add(by_k[a2][k2 - 1], u, S);
+        if constexpr (L::c(i, 0) == 0) add(rest, u, S);
     });
     s.drho = rest + ((by_k[0][0] + by_k[0][1]) + by_k[0][2]);
     for (int a = 0; a < D; ++a)
@@ -635,71 +685,69 @@ __device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T b
 
     // orbits on the axes first: they need no mixed coefficient, so the populations
     // they take are gone before those are formed (two FP64 registers a lane)
-    static_for<0, 3 * L::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value % L::Q, n = decltype(I)::value / L::Q + 1;
-        if constexpr (orbit_rep<L>(i) && Orbit<L>(i).n == n) {
-            constexpr Orbit<L> o(i);
-            constexpr double w = L::wshell(L::shell(i)) * SC::template scale<i>();
-            constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
-            constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
-            // k^2 (K + k^2 Q) of one axis, and the odd part's G + k^2 H
-            auto even1 = [&](auto A, T acc) {
-                constexpr int a = decltype(A)::value, k = L::c(i, a);
-                if constexpr (EQ == 4) return fma_t(T(k * k), fma_t(T(k * k), Q[a], K[a]), acc);
-                else return fma_t(T(k * k), K[a], acc);
-            };
-            auto odd1 = [&](auto A) {
-                constexpr int a = decltype(A)::value, k = L::c(i, a);
-                T v = O[a];
-                if constexpr (CUBIC) {
-                    v = fma_t(T(k * k), H[a][a], v);
-                    static_for<0, D>([&](auto B) {
-                        constexpr int b = decltype(B)::value, kb = L::c(i, b);
-                        if constexpr (b != a && kb != 0) v = fma_t(T(kb * kb), H[a][b], v);
-                    });
-                }
-                return T(w * k) * v;
-            };
-            auto cross = [&](auto A, auto B) {
-                constexpr int a = decltype(A)::value, b = decltype(B)::value;
-                constexpr int ka = L::c(i, a), kb = L::c(i, b);
-                T v = Kab[a][b];
-                if constexpr (EQ == 4)
-                    v = fma_t(T(kb * kb), Qab[1], fma_t(T(ka * ka), Qab[0], v));
-                return T(w * ka * kb) * v;
-            };
-            auto emit = [&](auto J, T ev, T od) {
-                constexpr int ip = o.plus(i, decltype(J)::value);
-                constexpr int im = opposite<L>(ip);
-                cb(std::integral_constant<int, ip>{}, std::integral_constant<int, im>{}, ev, od);
-            };
-            using A0 = std::integral_constant<int, a0>;
-            using A1 = std::integral_constant<int, a1>;
-            using A2 = std::integral_constant<int, a2>;
-            T e = even1(A0{}, C);
-            if constexpr (o.n == 1) {
-                emit(std::integral_constant<int, 0>{}, T(w) * e, odd1(A0{}));
-            } else if constexpr (o.n == 2) {
-                e = even1(A1{}, e);
-                if constexpr (EQ == 4) e = fma_t(T(k0 * k0 * k1 * k1), Qxy, e);
-                e *= T(w);
-                const T x = cross(A0{}, A1{});
-                const T p = odd1(A0{}), q = odd1(A1{});
-                emit(std::integral_constant<int, 0>{}, e + x, p + q);
-                emit(std::integral_constant<int, 1>{}, e - x, p - q);
-            } else {
-                e = T(w) * even1(A2{}, even1(A1{}, e));
-                const T x = cross(A0{}, A1{}), y = cross(A0{}, A2{}), z = cross(A1{}, A2{});
-                const T p = odd1(A0{}), q = odd1(A1{}), v = odd1(A2{});
-                const T h = CUBIC ? T(w * k0 * k1 * k2) * Hxyz : T(0);
-                // signs (+, s1, s2): even e + s1 x + s2 y + s1 s2 z, odd p + s1 q + s2 v + s1 s2 h
-                const T ex = e + x, em = e - x, yz = y + z, ym = y - z;
-                const T pq = p + q, pm = p - q, vh = v + h, vm = v - h;
-                emit(std::integral_constant<int, 0>{}, ex + yz, pq + vh);
-                emit(std::integral_constant<int, 1>{}, ex - yz, pq - vh);
-                emit(std::integral_constant<int, 2>{}, em + ym, pm + vm);
-                emit(std::integral_constant<int, 3>{}, em - ym, pm - vm);
+    static_for<0, ORBITS<L>.n>([&](auto I) {
+        constexpr int i = ORBITS<L>.rep[decltype(I)::value];
+        constexpr Orbit<L> o(i);
+        constexpr double w = L::wshell(L::shell(i)) * SC::template scale<i>();
+        constexpr int a0 = o.ax[0], a1 = o.ax[1], a2 = o.ax[2];
+        constexpr int k0 = L::c(i, a0), k1 = L::c(i, a1), k2 = L::c(i, a2);
+        // k^2 (K + k^2 Q) of one axis, and the odd part's G + k^2 H
+        auto even1 = [&](auto A, T acc) {
+            constexpr int a = decltype(A)::value, k = L::c(i, a);
+            if constexpr (EQ == 4) return fma_t(T(k * k), fma_t(T(k * k), Q[a], K[a]), acc);
+            else return fma_t(T(k * k), K[a], acc);
+        };
+        auto odd1 = [&](auto A) {
+            constexpr int a = decltype(A)::value, k = L::c(i, a);
+            T v = O[a];
+            if constexpr (CUBIC) {
+                v = fma_t(T(k * k), H[a][a], v);
+                static_for<0, D>([&](auto B) {
+                    constexpr int b = decltype(B)::value, kb = L::c(i, b);
+                    if constexpr (b != a && kb != 0) v = fma_t(T(kb * kb), H[a][b], v);
+                });
             }
+            return T(w * k) * v;
+        };
+        auto cross = [&](auto A, auto B) {
+            constexpr int a = decltype(A)::value, b = decltype(B)::value;
+            constexpr int ka = L::c(i, a), kb = L::c(i, b);
+            T v = Kab[a][b];
+            if constexpr (EQ == 4)
+                v = fma_t(T(kb * kb), Qab[1], fma_t(T(ka * ka), Qab[0], v));
+            return T(w * ka * kb) * v;
+        };
+        auto emit = [&](auto J, T ev, T od) {
+            constexpr int ip = o.plus(i, decltype(J)::value);
+            constexpr int im = opposite<L>(ip);
+            cb(std::integral_constant<int, ip>{}, std::integral_constant<int, im>{}, ev, od);
+        };
+        using A0 = std::integral_constant<int, a0>;
+        using A1 = std::integral_constant<int, a1>;
+        using A2 = std::integral_constant<int, a2>;
+        T e = even1(A0{}, C);
+        if constexpr (o.n == 1) {
+            emit(std::integral_constant<int, 0>{}, T(w) * e, odd1(A0{}));
+        } else if constexpr (o.n == 2) {
+            e = even1(A1{}, e);
+            if constexpr (EQ == 4) e = fma_t(T(k0 * k0 * k1 * k1), Qxy, e);
+            e *= T(w);
+            const T x = cross(A0{}, A1{});
+            const T p = odd1(A0{}), q = odd1(A1{});
+            emit(std::integral_constant<int, 0>{}, e + x, p + q);
+            emit(std::integral_constant<int, 1>{}, e - x, p - q);
+        } else {
+            e = T(w) * even1(A2{}, even1(A1{}, e));
+            const T x = cross(A0{}, A1{}), y = cross(A0{}, A2{}), z = cross(A1{}, A2{});
+            const T p = odd1(A0{}), q = odd1(A1{}), v = odd1(A2{});
+            const T h = CUBIC ? T(w * k0 * k1 * k2) * Hxyz : T(0);
+            // signs (+, s1, s2): even e + s1 x + s2 y + s1 s2 z, odd p + s1 q + s2 v + s1 s2 h
+            const T ex = e + x, em = e - x, yz = y + z, ym = y - z;
+            const T pq = p + q, pm = p - q, vh = v + h, vm = v - h;
+            emit(std::integral_constant<int, 0>{}, ex + yz, pq + vh);
+            emit(std::integral_constant<int, 1>{}, ex - yz, pq - vh);
+            emit(std::integral_constant<int, 2>{}, em + ym, pm + vm);
+            emit(std::integral_constant<int, 3>{}, em - ym, pm - vm);
         }
     });
 }
@@ -746,6 +794,7 @@ struct BatchLaunch {
     int64_t blocks;         // 0: one block per tile; > 0: persistent walk
     hipStream_t stream;
     bool walls;             // some member has plates (the kernel variant that handles them)
+    int64_t bytes;          // one population buffer of every member together, whole lines
 };
 hipError_t launch_multi_step(int lat, int storage, int eq, int fo, const BatchLaunch &bl);
 // plates: emission tables, the row sums of a state no step produced, and the

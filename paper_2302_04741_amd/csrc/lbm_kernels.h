@@ -147,7 +147,7 @@ __device__ __forceinline__ double wall_emitted(const WallDesc &wd, const GridDim
     return rw * wd.e[side * (L::Q + 1) + i] - w * rho0;
 }
 
-template <class L, class S, class T, bool WALLS = false>
+template <class L, class S, class T, bool WALLS = false, int LD = BUF_DEFAULT>
 __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &gd, int x, int y,
                                        int z, T (&h)[L::Q], const WallDesc *wd = nullptr,
                                        double rho0 = 0.0)
@@ -178,7 +178,7 @@ __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &
             }
         }
         h[i] = Codec<L, S>::template load_scaled<i, T>(
-            BufIO<S>::load(planes.at(i), xs[cx + 3], zs[cz + 3] + ys[cy + 3]));
+            BufIO<S>::template load<LD>(planes.at(i), xs[cx + 3], zs[cz + 3] + ys[cy + 3]));
     });
 }
 
@@ -209,7 +209,8 @@ struct StepShape {
 // 227 / 234, 224^3 614 / 657, 256^3 913 / 957 (1024 threads, 16 wavefronts: 942),
 // D2Q37 2048^2 220 / 226, 3000^2 475 / 500; below that size it gains or loses 2%,
 // and F16, with half the bytes a wavefront, loses (256^3 700 / 496).
-constexpr int64_t STEP_LARGE_BYTES = int64_t(400) << 20;
+constexpr int64_t MIB = int64_t(1) << 20;
+constexpr int64_t STEP_LARGE_BYTES = 400 * MIB;
 constexpr unsigned STEP_LDS_PER_CU = 160u << 10;
 
 template <class S> inline StepShape step_shape(int64_t buffer_bytes, int threads)
@@ -219,6 +220,36 @@ template <class S> inline StepShape step_shape(int64_t buffer_bytes, int threads
     bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
     const bool limit = large && (bx == 256 || bx == 512);
     return StepShape{bx, limit ? STEP_LDS_PER_CU * unsigned(bx) / 512u : 0u};
+}
+
+// Cache policy for a population buffer of T bytes (whole lines), measured from
+// T = 10 MB to 5 GB (table at Policy).  Both buffers fit the memory-side cache up
+// to 128 MiB each.  Past it, up to 400 MiB, KEEP_WRITES gains 3-18% on D3Q39 (F16:
+// to 200 MiB; past that its loads of half a line a wavefront lose 10% with nt) and
+// on D2Q37 from 240 MiB; D2Q37 below that re-reads the lines at its blocks' row
+// ends (a block is a quarter of a row) and wants default loads: up to 192 MiB
+// RESIDENT swept backwards still gains 3-8%, between 192 and 240 MiB and for F16
+// nothing gains.
+struct StepPolicy {
+    Policy policy;
+    bool reversed;  // odd steps sweep backwards
+};
+template <int LAT, class S> inline StepPolicy step_policy(int64_t T)
+{
+    if (T <= 128 * MIB) return {Policy::RESIDENT, false};
+    if (LAT == 1) {
+        if (T <= (sizeof(S) == 2 ? 200 : 400) * MIB) return {Policy::KEEP_WRITES, true};
+    } else if (sizeof(S) > 2) {
+        if (T <= 192 * MIB) return {Policy::RESIDENT, true};
+        if (T > 240 * MIB && T <= 400 * MIB) return {Policy::KEEP_WRITES, true};
+    }
+    return {Policy::STREAM, true};
+}
+// Bytes of one population buffer in whole 128-byte lines.
+template <int LAT, class S> inline int64_t buffer_lines_bytes(const GridDims &gd)
+{
+    return int64_t(Lattice<LAT>::Q) * gd.ny * gd.nz *
+           ((int64_t(gd.nx) * int64_t(sizeof(S)) + 127) / 128 * 128);
 }
 
 // The fused update of one cell (x, y, z): gather, moments, equilibrium, stress,
@@ -233,7 +264,7 @@ template <class S> inline StepShape step_shape(int64_t buffer_bytes, int threads
 // resource made for each access it was 1860 and 2211.  Step of D2Q37 64^2 FP64:
 // 5.7 -> 4.7 us, of the plated 3 x 150 channel 15.3 -> 12.2 us, of D2Q37 256^2 FP32
 // 8.4 -> 7.9 us; at 1024^2 and above the memory time hid most of it already.
-template <int LAT, class S, int EQ, int FO, bool WALLS = false>
+template <int LAT, class S, int EQ, int FO, Policy P, bool WALLS = false>
 __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict__ B,
                                           const GridDims &gd, const ForceDesc &fd,
                                           const StepCoef &co, int x, int y, int z,
@@ -251,7 +282,7 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
     using C = Codec<L, S>;
     SrStream rng{C::STOCHASTIC ? sr_key(uint32_t(cell), step) : 0u};
     T h[L::Q];
-    gather<L, S, T, WALLS>(A, gd, x, y, z, h, wd, co.rho0);
+    gather<L, S, T, WALLS, CacheBits<P>::load>(A, gd, x, y, z, h, wd, co.rho0);
     T g[3];
     load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
 
@@ -290,11 +321,12 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
         constexpr int im = decltype(IM)::value;
         auto relaxed = [&](T hi, T sign_od) { return fma_t(omc, hi, ev + sign_od); };
         const S sp = C::template store_scaled<ip, T>(relaxed(h[ip], od), rng);
-        BufIO<S>::store(sp, planes.at(ip), xo, ro);
+        constexpr int ST = CacheBits<P>::store;
+        BufIO<S>::template store<ST>(sp, planes.at(ip), xo, ro);
         account(IP, sp);
         if constexpr (im >= 0) {
             const S sm = C::template store_scaled<im, T>(relaxed(h[im], -od), rng);
-            BufIO<S>::store(sm, planes.at(im), xo, ro);
+            BufIO<S>::template store<ST>(sm, planes.at(im), xo, ro);
             account(IM, sm);
         }
     });
@@ -348,26 +380,32 @@ __device__ __forceinline__ bool wave_cell(const GridDims &gd, uint32_t wave, int
 // schedule takes 170).
 template <class S> constexpr int step_min_waves() { return sizeof(S) == 8 ? 3 : 5; }
 
-template <int LAT, class S, int EQ, int FO>
+// The block's place in the sweep: the reversed sweep of odd steps (see Policy).
+__device__ __forceinline__ uint32_t swept_block(int backwards)
+{
+    return backwards ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+}
+
+template <int LAT, class S, int EQ, int FO, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     __attribute__((amdgpu_waves_per_eu(step_min_waves<S>(), 8)))
     step_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd, ForceDesc fd,
-                StepCoef co, uint32_t *ctr, int cur)
+                StepCoef co, uint32_t *ctr, int cur, int backwards)
 {
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) +
-                                                         (threadIdx.x >> 6));
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(
+        swept_block(backwards) * (blockDim.x >> 6) + (threadIdx.x >> 6));
     const uint32_t step = step_number<S>(ctr, cur);
     advance_step_number<S>(ctr, cur, step, wave == 0 && threadIdx.x == 0);
     int x, y, z;
     if (!wave_cell(gd, wave, x, y, z)) return;
-    step_cell<LAT, S, EQ, FO>(A, B, gd, fd, co, x, y, z, step);
+    step_cell<LAT, S, EQ, FO, P>(A, B, gd, fd, co, x, y, z, step);
 }
 
 // K7 (diagnostic): the memory traffic of K1 alone -- every population read
 // from its pull source and written unchanged at the cell's own slot of the
 // other buffer, K1's work split, no arithmetic.  Its rate is the ceiling of
 // K1's access pattern on the device.
-template <int LAT, class S>
+template <int LAT, class S, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     pattern_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd)
 {
@@ -377,13 +415,13 @@ __global__ void __launch_bounds__(step_max_threads<S>())
     int x, y, z;
     if (!wave_cell(gd, wave, x, y, z)) return;
     S h[L::Q];
-    gather<L, S, S>(A, gd, x, y, z, h);
+    gather<L, S, S, false, CacheBits<P>::load>(A, gd, x, y, z, h);
     const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
     const uint32_t ro = uint32_t((int64_t(z) * gd.ny + y) * gd.px) * uint32_t(sizeof(S));
     PlaneWalk planes(B, uint32_t(gd.P * int64_t(sizeof(S))));
     static_for<0, L::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        BufIO<S>::store(h[i], planes.at(i), xo, ro);
+        BufIO<S>::template store<CacheBits<P>::store>(h[i], planes.at(i), xo, ro);
     });
 }
 
@@ -391,7 +429,7 @@ __global__ void __launch_bounds__(step_max_threads<S>())
 // the wavefronts of the rows next to a plate (y < 3 or y >= ny - 3, a uniform
 // test) take the plates' emission in place of the sources behind them and
 // write the partial sums of the state they produce.
-template <int LAT, class S, int EQ, int FO>
+template <int LAT, class S, int EQ, int FO, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     wall_step_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd, ForceDesc fd,
                      StepCoef co, WallDesc wd, uint32_t *ctr, int cur)
@@ -403,9 +441,9 @@ __global__ void __launch_bounds__(step_max_threads<S>())
     int x, y, z;
     if (!wave_cell(gd, wave, x, y, z)) return;
     if (y < 3 || y >= gd.ny - 3)
-        step_cell<LAT, S, EQ, FO, true>(A, B, gd, fd, co, x, y, z, step, &wd);
+        step_cell<LAT, S, EQ, FO, P, true>(A, B, gd, fd, co, x, y, z, step, &wd);
     else
-        step_cell<LAT, S, EQ, FO>(A, B, gd, fd, co, x, y, z, step);
+        step_cell<LAT, S, EQ, FO, P>(A, B, gd, fd, co, x, y, z, step);
 }
 
 // ---------------------------------------------------------------------------
@@ -422,14 +460,15 @@ __global__ void __launch_bounds__(step_max_threads<S>())
 // plates) updates the rows next to a member's plates as K1c does; periodic
 // batches keep the variant without that code.
 // ---------------------------------------------------------------------------
-template <int LAT, class S, int EQ, int FO, bool WALLS>
+template <int LAT, class S, int EQ, int FO, Policy P, bool WALLS>
 __global__ void __launch_bounds__(256)
     multi_step_kernel(const int64_t *__restrict__ begin, const TileSim *__restrict__ sims,
-                      int nsims, int64_t ntiles, int parity)
+                      int nsims, int64_t ntiles, int parity, int backwards)
 {
     const int64_t nw = int64_t(gridDim.x) * (blockDim.x >> 6);
-    int64_t t = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    for (; t < ntiles; t += nw) {
+    int64_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    for (; w < ntiles; w += nw) {
+        const int64_t t = backwards ? ntiles - 1 - w : w;
         // the simulation owning tile t: last k with begin[k] <= t (uniform)
         int lo = 0, hi = nsims - 1;
         while (lo < hi) {
@@ -456,13 +495,14 @@ __global__ void __launch_bounds__(256)
         if constexpr (WALLS) {
             // a member between plates: its rows next to a plate as in K1c
             if (sd.wd.on && (y < 3 || y >= sd.gd.ny - 3)) {
-                WallDesc w = sd.wd;
-                w.par = c;
-                step_cell<LAT, S, EQ, FO, true>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step, &w);
+                WallDesc wd = sd.wd;
+                wd.par = c;
+                step_cell<LAT, S, EQ, FO, P, true>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step,
+                                                   &wd);
                 continue;
             }
         }
-        step_cell<LAT, S, EQ, FO>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step);
+        step_cell<LAT, S, EQ, FO, P>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step);
     }
 }
 

@@ -33,21 +33,44 @@ template <int LAT, class F> hipError_t with_eq_fo(int eq, int fo, F &&f)
     return r;
 }
 
+// f(policy constant) for a runtime policy
+template <class F> hipError_t with_policy(Policy p, F &&f)
+{
+    switch (p) {
+    case Policy::RESIDENT: return f(std::integral_constant<Policy, Policy::RESIDENT>{});
+    case Policy::KEEP_WRITES: return f(std::integral_constant<Policy, Policy::KEEP_WRITES>{});
+    default: return f(std::integral_constant<Policy, Policy::STREAM>{});
+    }
+}
+
+// The same for the kernels with plates, which come in two of them: channels are
+// small or, like their periodic neighbours in size, streamed.
+template <class F> hipError_t with_wall_policy(Policy p, F &&f)
+{
+    if (p == Policy::RESIDENT) return f(std::integral_constant<Policy, Policy::RESIDENT>{});
+    return f(std::integral_constant<Policy, Policy::STREAM>{});
+}
+
 template <int LAT, class S>
 hipError_t launch_step_ls(int eq, int fo, const void *A, void *B, const GridDims &gd,
                           const ForceDesc &fd, const StepCoef &co, const LaunchCfg &lc)
 {
     // blocks of bx/64 wavefronts, one wavefront per 64 cells of a row
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    const StepShape sh =
-        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
+    const StepShape sh = step_shape<S>(bytes, lc.block);
+    const StepPolicy sp = step_policy<LAT, S>(bytes);
     const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
-        hipLaunchKernelGGL((step_kernel<LAT, S, decltype(E)::value, decltype(O)::value>), grid,
-                           dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A),
-                           static_cast<S *>(B), gd, fd, co, lc.ctr, lc.cur);
-        return hipGetLastError();
+        return with_policy(sp.policy, [&](auto P) {
+            hipLaunchKernelGGL((step_kernel<LAT, S, decltype(E)::value, decltype(O)::value,
+                                            decltype(P)::value>),
+                               grid, dim3(sh.threads), sh.lds, lc.stream,
+                               static_cast<const S *>(A), static_cast<S *>(B), gd, fd, co, lc.ctr,
+                               lc.cur, int(sp.reversed && lc.cur));
+            return hipGetLastError();
+        });
     });
 }
 
@@ -56,13 +79,15 @@ hipError_t launch_pattern_ls(const void *A, void *B, const GridDims &gd, const L
 {
     // the launch shape of the step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    const StepShape sh =
-        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
+    const StepShape sh = step_shape<S>(bytes, lc.block);
     const int64_t wpb = sh.threads / 64;
-    hipLaunchKernelGGL((pattern_kernel<LAT, S>), dim3(unsigned((waves + wpb - 1) / wpb)),
-                       dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A), static_cast<S *>(B),
-                       gd);
-    return hipGetLastError();
+    return with_policy(step_policy<LAT, S>(bytes).policy, [&](auto P) {
+        hipLaunchKernelGGL((pattern_kernel<LAT, S, decltype(P)::value>),
+                           dim3(unsigned((waves + wpb - 1) / wpb)), dim3(sh.threads), sh.lds,
+                           lc.stream, static_cast<const S *>(A), static_cast<S *>(B), gd);
+        return hipGetLastError();
+    });
 }
 
 template <int LAT, class S>
@@ -75,17 +100,23 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     const int64_t need = (bl.ntiles + wpb - 1) / wpb;
     int64_t grid = bl.blocks > 0 ? std::min(bl.blocks, need) : need;
     grid = std::min<int64_t>(grid, 0x7fffffff);
+    const StepPolicy sp = step_policy<LAT, S>(bl.bytes);
+    const int backwards = int(sp.reversed && bl.parity);
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         constexpr int EQ = decltype(E)::value, FO = decltype(O)::value;
         if (bl.walls)
-            hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, true>), dim3(unsigned(grid)),
-                               dim3(unsigned(bl.threads)), 0, bl.stream, bl.begin, bl.table,
-                               bl.nsims, bl.ntiles, bl.parity);
-        else
-            hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, false>), dim3(unsigned(grid)),
-                               dim3(unsigned(bl.threads)), 0, bl.stream, bl.begin, bl.table,
-                               bl.nsims, bl.ntiles, bl.parity);
-        return hipGetLastError();
+            return with_wall_policy(sp.policy, [&](auto P) {
+                hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, true>),
+                                   dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
+                                   bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards);
+                return hipGetLastError();
+            });
+        return with_policy(sp.policy, [&](auto P) {
+            hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, false>),
+                               dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
+                               bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards);
+            return hipGetLastError();
+        });
     });
 }
 
@@ -133,15 +164,19 @@ hipError_t launch_wall_step_ls(int eq, int fo, const void *A, void *B, const Gri
 {
     // the work split of the periodic step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
-    const StepShape sh =
-        step_shape<S>(int64_t(Lattice<LAT>::Q) * gd.P * int64_t(sizeof(S)), lc.block);
+    const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
+    const StepShape sh = step_shape<S>(bytes, lc.block);
     const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
-        hipLaunchKernelGGL((wall_step_kernel<LAT, S, decltype(E)::value, decltype(O)::value>),
-                           grid, dim3(sh.threads), sh.lds, lc.stream, static_cast<const S *>(A),
-                           static_cast<S *>(B), gd, fd, co, lc.walls, lc.ctr, lc.cur);
-        return hipGetLastError();
+        return with_wall_policy(step_policy<LAT, S>(bytes).policy, [&](auto P) {
+            hipLaunchKernelGGL((wall_step_kernel<LAT, S, decltype(E)::value, decltype(O)::value,
+                                                 decltype(P)::value>),
+                               grid, dim3(sh.threads), sh.lds, lc.stream,
+                               static_cast<const S *>(A), static_cast<S *>(B), gd, fd, co,
+                               lc.walls, lc.ctr, lc.cur);
+            return hipGetLastError();
+        });
     });
 }
 
