@@ -237,9 +237,9 @@ LBM_API lbm_status lbm_set_stream(lbm_sim *s, void *hip_stream);
 /* Kernel launch shape of the step of eq. (lbm) (an implementation choice, not
  * the paper's): threads per block (64, 128, 256, 512 or
  * 1024; FP64 storage uses at most 256), i.e. wavefronts per block, each
- * wavefront updating 64 consecutive cells of one row.  0 restores the default
- * (256; 128 for FP64 storage; 512 for FP32 storage whose populations take at
- * least 400 MiB a buffer).  Results do not depend on it. */
+ * wavefront updating 64 consecutive cells of one row.  0 restores the default,
+ * which follows the storage and the size of the grid.  Results do not depend
+ * on it. */
 LBM_API lbm_status lbm_set_block(lbm_sim *s, int32_t threads);
 
 /* Relaxation time per cell (Sec. 3 of the paper: tau = mu/(rho theta) keeps the

@@ -210,13 +210,46 @@ struct StepShape {
 // D2Q37 2048^2 220 / 226, 3000^2 475 / 500; below that size it gains or loses 2%,
 // and F16, with half the bytes a wavefront, loses (256^3 700 / 496).
 constexpr int64_t MIB = int64_t(1) << 20;
+constexpr int64_t STEP_CACHED_BYTES = 128 * MIB;  // two such buffers fit the memory-side cache
 constexpr int64_t STEP_LARGE_BYTES = 400 * MIB;
 constexpr unsigned STEP_LDS_PER_CU = 160u << 10;
 
-template <class S> inline StepShape step_shape(int64_t buffer_bytes, int threads)
+// Grids of a few wavefronts a SIMD (1024 SIMDs on the chip), both buffers cached:
+// what counts there is how the blocks spread over the CUs in one round, and the
+// widths measured best follow the number of wavefronts (us a step, against 256
+// threads, 128 for FP64):
+//   up to 256: 64 threads, a wavefront a CU (FP64 64^2 3.8 / 4.1, 12^3 4.4 / 5.4,
+//     FP32 100x128 3.8 / 4.3, plated 3 x 150 FP64 10.6 / 12.1);
+//   FP64 to 4096: 64 (256^2 9.3 / 10.5, 40^3 8.7 / 9.9, 64^3 24 / 35);
+//   FP32 512-1280: 512 (200^2 5.4 / 6.0, 250x300 7.0 / 8.9, 33^3 5.6 / 6.2); F16 on
+//     D2Q37 1100-2048: 512 (320^2 6.6 / 7.3);
+//   FP32 to 2048: 1024 on D2Q37 (320^2 8.4 / 9.6), 64 on D3Q39 (40^3 7.0 / 8.0);
+//   FP32 and F16 to 4096 (F16 on D3Q39 from 3072): 1024, one block a CU at most
+//     (FP32 400x300 8.6 / 10.7, 512^2 12.9 / 14.9, F16 512^2 8.3 / 10.5, 64^3 8.1 / 11.2);
+//   beyond, FP32 on D2Q37: 512 (600^2 17.1 / 18.5, 700^2 23.3 / 24.8).
+// 0: no preference.
+template <int LAT, class S> inline int small_grid_threads(int64_t waves)
+{
+    if (waves <= 256) return 64;
+    if (sizeof(S) == 8) return waves <= 4096 ? 64 : 0;
+    if (sizeof(S) == 4) {
+        if (waves <= 512) return 0;
+        if (waves <= 1280) return 512;
+        if (waves <= 2048) return LAT == 0 ? 1024 : 64;
+        if (waves <= 4096) return 1024;
+        return LAT == 0 ? 512 : 0;
+    }
+    if (LAT == 0 && waves > 1100 && waves <= 2048) return 512;
+    return waves > (LAT == 0 ? 2048 : 3072) && waves <= 4096 ? 1024 : 0;
+}
+
+template <int LAT, class S>
+inline StepShape step_shape(int64_t buffer_bytes, int64_t waves, int threads)
 {
     const bool large = sizeof(S) == 4 && buffer_bytes >= STEP_LARGE_BYTES;
-    int bx = threads > 0 ? threads : (sizeof(S) == 8 ? 128 : (large ? 512 : 256));
+    int bx = threads;
+    if (bx <= 0 && buffer_bytes <= STEP_CACHED_BYTES) bx = small_grid_threads<LAT, S>(waves);
+    if (bx <= 0) bx = sizeof(S) == 8 ? 128 : (large ? 512 : 256);
     bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
     const bool limit = large && (bx == 256 || bx == 512);
     return StepShape{bx, limit ? STEP_LDS_PER_CU * unsigned(bx) / 512u : 0u};
@@ -236,7 +269,7 @@ struct StepPolicy {
 };
 template <int LAT, class S> inline StepPolicy step_policy(int64_t T)
 {
-    if (T <= 128 * MIB) return {Policy::RESIDENT, false};
+    if (T <= STEP_CACHED_BYTES) return {Policy::RESIDENT, false};
     if (LAT == 1) {
         if (T <= (sizeof(S) == 2 ? 200 : 400) * MIB) return {Policy::KEEP_WRITES, true};
     } else if (sizeof(S) > 2) {

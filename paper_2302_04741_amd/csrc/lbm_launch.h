@@ -58,7 +58,7 @@ hipError_t launch_step_ls(int eq, int fo, const void *A, void *B, const GridDims
     // blocks of bx/64 wavefronts, one wavefront per 64 cells of a row
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
     const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
-    const StepShape sh = step_shape<S>(bytes, lc.block);
+    const StepShape sh = step_shape<LAT, S>(bytes, waves, lc.block);
     const StepPolicy sp = step_policy<LAT, S>(bytes);
     const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
@@ -80,7 +80,7 @@ hipError_t launch_pattern_ls(const void *A, void *B, const GridDims &gd, const L
     // the launch shape of the step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
     const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
-    const StepShape sh = step_shape<S>(bytes, lc.block);
+    const StepShape sh = step_shape<LAT, S>(bytes, waves, lc.block);
     const int64_t wpb = sh.threads / 64;
     return with_policy(step_policy<LAT, S>(bytes).policy, [&](auto P) {
         hipLaunchKernelGGL((pattern_kernel<LAT, S, decltype(P)::value>),
@@ -165,7 +165,7 @@ hipError_t launch_wall_step_ls(int eq, int fo, const void *A, void *B, const Gri
     // the work split of the periodic step (blocks of bx/64 row wavefronts)
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz;
     const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
-    const StepShape sh = step_shape<S>(bytes, lc.block);
+    const StepShape sh = step_shape<LAT, S>(bytes, waves, lc.block);
     const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
