@@ -895,16 +895,6 @@ __global__ void __launch_bounds__(256)
 // The partition and the reduction order do not depend on the grid or launch
 // shape of the step, so the result is bitwise reproducible.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double block_sum_256(double v, double *lds)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) lds[wid] = v;
-    __syncthreads();
-    return (lds[0] + lds[1]) + (lds[2] + lds[3]);
-}
-
 // Stage 1: block b sums the cells of a fixed run of grid rows, every lane
 // holding one FP64 accumulator per population: the block's cells are taken
 // in order, lane t the t-th of every 256, all Q planes of a cell loaded
@@ -942,23 +932,29 @@ __global__ void __launch_bounds__(256)
     __syncthreads();
     if (threadIdx.x < L::Q) {
         const int i = threadIdx.x;
-        partials[int64_t(blockIdx.x) * L::Q + i] = (lds[0][i] + lds[1][i]) + (lds[2][i] + lds[3][i]);
+        partials[int64_t(i) * TOTALS_BLOCKS + blockIdx.x] =
+            (lds[0][i] + lds[1][i]) + (lds[2][i] + lds[3][i]);
     }
 }
 
+// Stage 2: a wavefront adds the 512 slices of one plane (8 a lane, then a tree),
+// 16 planes at a time: 4 us.  One block adding plane after plane, with two barriers
+// each, took 37 us, more than stage 1 of every grid below 10^6 cells.
 template <int LAT>
-__global__ void __launch_bounds__(256) totals_stage2(const double *__restrict__ partials,
-                                                     double *__restrict__ out, GridDims gd,
-                                                     StepCoef co)
+__global__ void __launch_bounds__(1024) totals_stage2(const double *__restrict__ partials,
+                                                      double *__restrict__ out, GridDims gd,
+                                                      StepCoef co)
 {
     using L = Lattice<LAT>;
-    __shared__ double lds[4];
     __shared__ double Hi[L::Q];
-    for (int i = 0; i < L::Q; ++i) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < TOTALS_BLOCKS; b += 256) v += partials[int64_t(b) * L::Q + i];
-        v = block_sum_256(v, lds);
-        if (threadIdx.x == 0) Hi[i] = v;
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x >> 6; i < L::Q; i += 16) {
+        const double *p = partials + int64_t(i) * TOTALS_BLOCKS + lane;
+        double v = p[0];
+#pragma unroll
+        for (int k = 1; k < TOTALS_BLOCKS / 64; ++k) v += p[64 * k];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) Hi[i] = v;
     }
     __syncthreads();
     if (threadIdx.x == 0) {

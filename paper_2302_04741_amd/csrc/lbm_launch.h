@@ -229,7 +229,7 @@ hipError_t launch_totals_l(int storage, const void *A, double *partials, double 
                            static_cast<const __half *>(A), partials, gd, by_nx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((totals_stage2<LAT>), dim3(1), dim3(256), 0, stream, partials, out_dev,
+    hipLaunchKernelGGL((totals_stage2<LAT>), dim3(1), dim3(1024), 0, stream, partials, out_dev,
                        gd, co);
     return hipGetLastError();
 }
