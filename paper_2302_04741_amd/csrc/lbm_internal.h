@@ -783,6 +783,10 @@ hipError_t launch_totals(int lat, int storage, const void *A, double *partials, 
                          const GridDims &gd, const StepCoef &co, hipStream_t stream);
 hipError_t launch_convert(int storage, const double *src, void *dst, int64_t n,
                           hipStream_t stream);
+// dense rows (nx values each, back to back) out of (exporting) or into the padded
+// rows of all Q planes; `dense` aligned to the stored type (rows.hip)
+hipError_t launch_copy_rows(int storage, void *padded, void *dense, const GridDims &gd, int Q,
+                            bool exporting, hipStream_t stream);
 // One launch of the multi-grid step: tile list, its members, launch shape.
 struct BatchLaunch {
     const int64_t *begin;   // device: first tile of member k (k < nsims), ascending
