@@ -198,12 +198,15 @@ bool on_this_device(const void *p)
 // lanes take half the time of the runtime's 2-D copy there (D2Q37 1017^2 FP32 54
 // us against 107); where the rows have no padding that copy is one contiguous
 // run at full rate (6.1 TB/s on D3Q39 256^3 F16), and it takes what the kernel
-// cannot: memory of another device, or not aligned to the stored type.
+// cannot: memory of another device, or not aligned to the stored type.  Small
+// states keep it too: either way they take a launch, and the pointer query of the
+// kernel's path costs the host 0.5 us.
+constexpr size_t ROW_KERNEL_MIN_BYTES = size_t(2) << 20;
 hipError_t copy_populations(const lbm_sim *s, void *dense, bool exporting)
 {
     const size_t sb = storage_bytes(s->p.storage);
-    if (s->gd.px != s->gd.nx && reinterpret_cast<uintptr_t>(dense) % sb == 0 &&
-        on_this_device(dense))
+    if (s->gd.px != s->gd.nx && lbm_population_bytes(s) >= ROW_KERNEL_MIN_BYTES &&
+        reinterpret_cast<uintptr_t>(dense) % sb == 0 && on_this_device(dense))
         return launch_copy_rows(s->p.storage, s->pop[s->cur], dense, s->gd, s->Q, exporting,
                                 s->stream);
     const size_t width = size_t(s->gd.nx) * sb, pitch = size_t(s->gd.px) * sb;

@@ -180,6 +180,32 @@ __device__ __forceinline__ void wall_densities_of(const WallDesc &wd, const Grid
     });
 }
 
+// Byte offsets of the pull sources x - c of one wavefront's cells: 7 per lane along
+// x; y and z are uniform over the wavefront, so each row offset is a scalar.  A
+// plane is < 4 GiB (checked at creation), so are all of them.
+template <class L, class S> struct PullOffsets {
+    uint32_t xs[7], ys[7], zs[7];
+    __device__ __forceinline__ PullOffsets(const GridDims &gd, int x, int y, int z, bool pin)
+    {
+        const uint32_t pitch = uint32_t(gd.px) * uint32_t(sizeof(S));
+        const uint32_t slab = pitch * uint32_t(gd.ny);
+#pragma unroll
+        for (int d = -3; d <= 3; ++d) {
+            xs[d + 3] = wrap_back(uint32_t(x), d, uint32_t(gd.nx)) * uint32_t(sizeof(S));
+            ys[d + 3] = wrap_back(uint32_t(y), d, uint32_t(gd.ny)) * pitch;
+            zs[d + 3] = (L::D == 3) ? wrap_back(uint32_t(z), d, uint32_t(gd.nz)) * slab : 0u;
+            if (pin) {  // uniform, but around branches some end up on the vector unit
+                ys[d + 3] = __builtin_amdgcn_readfirstlane(ys[d + 3]);
+                zs[d + 3] = __builtin_amdgcn_readfirstlane(zs[d + 3]);
+            }
+        }
+    }
+    __device__ __forceinline__ uint32_t row(int cy, int cz) const
+    {
+        return zs[cz + 3] + ys[cy + 3];
+    }
+};
+
 // With plates (WALLS, the rows next to one), a population whose source lies behind
 // the plate is the plate's emission into it, h_i = rw e_i - w_i rho0 with rw the
 // plate's density over the source's column.  Which ones do depends on c_y alone:
@@ -193,28 +219,13 @@ __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &
                                        int z, T (&h)[L::Q], const WallDesc *wd = nullptr,
                                        double rho0 = 0.0)
 {
-    // Byte offsets: 7 per lane along x; y and z are uniform over the wavefront, so
-    // each row offset and each plane resource is a scalar.  A plane is < 4 GiB
-    // (checked at creation), so are all of them.
-    const uint32_t pitch = uint32_t(gd.px) * uint32_t(sizeof(S));
-    const uint32_t slab = pitch * uint32_t(gd.ny);
-    uint32_t xs[7], ys[7], zs[7];
-#pragma unroll
-    for (int d = -3; d <= 3; ++d) {
-        xs[d + 3] = wrap_back(uint32_t(x), d, uint32_t(gd.nx)) * uint32_t(sizeof(S));
-        ys[d + 3] = wrap_back(uint32_t(y), d, uint32_t(gd.ny)) * pitch;
-        zs[d + 3] = (L::D == 3) ? wrap_back(uint32_t(z), d, uint32_t(gd.nz)) * slab : 0u;
-        if constexpr (WALLS) {  // uniform, but left alone some end up on the vector unit
-            ys[d + 3] = __builtin_amdgcn_readfirstlane(ys[d + 3]);
-            zs[d + 3] = __builtin_amdgcn_readfirstlane(zs[d + 3]);
-        }
-    }
+    const PullOffsets<L, S> at(gd, x, y, z, WALLS);
     const PlaneWalk first(A, uint32_t(gd.P * int64_t(sizeof(S))));
     auto fetch = [&](auto I, PlaneWalk &planes) {
         constexpr int i = decltype(I)::value;
         constexpr int cx = L::c(i, 0), cy = L::c(i, 1), cz = L::c(i, 2);
         h[i] = Codec<L, S>::template load_scaled<i, T>(
-            BufIO<S>::template load<LD>(planes.at(i), xs[cx + 3], zs[cz + 3] + ys[cy + 3]));
+            BufIO<S>::template load<LD>(planes.at(i), at.xs[cx + 3], at.row(cy, cz)));
     };
     if constexpr (!WALLS) {
         PlaneWalk planes = first;
@@ -481,6 +492,12 @@ __device__ __forceinline__ bool wave_cell(const GridDims &gd, uint32_t wave, int
     return x < gd.nx;
 }
 
+// The wavefront's number in a launch of whole wavefronts.
+__device__ __forceinline__ uint32_t block_wave()
+{
+    return __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+}
+
 // Wavefronts per SIMD the compiler must leave room for: FP32 arithmetic fits
 // five without spills; FP64 needs three (168 registers; left free, the D3Q39
 // schedule takes 170).
@@ -613,42 +630,35 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---------------------------------------------------------------------------
-// kernels off the step path: one thread per cell, blocks along x of one grid
-// row (y and z uniform over the block), arithmetic in the storage's own
+// kernels off the step path: one thread per cell, the step's work split in blocks
+// of 256 threads, arithmetic in the storage's own
 // precision (FP64 for FP64 storage, FP32 for FP32 and F16 storage; the
 // fields handed in and out stay FP64)
 // ---------------------------------------------------------------------------
-// h_i (unscaled) of the state in A at (x, y, z), the plates' emission in
-// place of sources behind them.
-template <class L, class S, class T>
-__device__ __forceinline__ void gather_state(const S *__restrict__ A, const GridDims &gd, int x,
-                                             int y, int z, T (&h)[L::Q], const WallDesc &wd,
-                                             double rho0)
-{
-    if (wd.on && (y < 3 || y >= gd.ny - 3))  // uniform over the block
-        gather<L, S, T, true>(A, gd, x, y, z, h, &wd, rho0);
-    else
-        gather<L, S, T>(A, gd, x, y, z, h);
-}
-
+// Each comes in two variants, without plates and with (WALLS: launched for a handle
+// that has them; every row then takes the gather that tests for a plate).  One
+// kernel choosing between two gathers had its 39 loads in two branches and waited
+// for some of them one by one.
 // ---------------------------------------------------------------------------
 // K2: initial state f~ = f0 - F/2 (sigma = 0), stored as h = f~ - w rho0 and
 // scattered so that the pull gather of the first step finds h_i(x) at
-// A[i][x - c_i].
+// A[i][x - c_i].  Bound by memory, by its shifted stores above all: default
+// (write-back) stores, since lines are completed by neighbouring wavefronts
+// (streamed or written through they cost 20-120% more).
 // ---------------------------------------------------------------------------
-template <int LAT, class S, int EQ, int FO>
-__global__ void __launch_bounds__(256)
+template <int LAT, class S, int EQ, int FO, bool WALLS>
+__global__ void __launch_bounds__(512)
     init_kernel(const double *__restrict__ rho, const double *__restrict__ u,
                 const double *__restrict__ theta, S *__restrict__ A, GridDims gd, ForceDesc fd,
-                StepCoef co, WallDesc wd)
+                StepCoef co)
 {
     using L = Lattice<LAT>;
     using T = typename ArithOf<S>::type;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= gd.nx) return;
+    int x, y, z;
+    if (!wave_cell(gd, block_wave(), x, y, z)) return;
     const int64_t N = gd.N;
-    const int64_t cell = (int64_t(z) * gd.ny + y) * gd.nx + x;
+    const int64_t row = int64_t(z) * gd.ny + y;
+    const int64_t cell = row * gd.nx + x;
 
     T g[3];
     load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
@@ -661,41 +671,39 @@ __global__ void __launch_bounds__(256)
         cs.g[a] = g[a];
         for (int b = 0; b < 3; ++b) cs.sig[a][b] = T(0);
     }
+    // the slot the first step pulls velocity i of this cell from is x - c_i
+    const PullOffsets<L, S> at(gd, x, y, z, true);
+    const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
+    const uint32_t ro = uint32_t(row * gd.px) * uint32_t(sizeof(S));
+    PlaneWalk planes(A, uint32_t(gd.P * int64_t(sizeof(S))));
     constexpr int FOI = FO == 4 ? 3 : FO;  // sigma = 0 at the start
     // h = w (rho - rho0) + (f0 - w rho) - F/2
     combo_pairs<L, T, EQ, FOI, true>(cs, T(1), T(-0.5), cs.drho,
                                      [&](auto IP, auto IM, T ev, T od) {
-        constexpr int ip = decltype(IP)::value;
-        constexpr int im = decltype(IM)::value;
         auto put = [&](auto II, T v) {
             constexpr int i = decltype(II)::value;
+            constexpr int cx = L::c(i, 0), cy = L::c(i, 1), cz = L::c(i, 2);
             const S sv = Codec<L, S>::template store<i, T>(v);
-            if (wd.on) {
+            const RsrcWords plane = planes.at(i);
+            if constexpr (cy != 0 && WALLS) {
                 // with plates: a population arriving from behind a plate has no
                 // slot (the plate emits it); one about to stream into a plate
                 // stays in its own node's slot
-                if (y + L::c(i, 1) < 0 || y + L::c(i, 1) >= gd.ny) {
-                    const int64_t own = (int64_t(z) * gd.ny + y) * gd.px + x;
-                    A[int64_t(i) * gd.P + own] = sv;
-                }
-                if (y - L::c(i, 1) < 0 || y - L::c(i, 1) >= gd.ny) return;
+                if (y + cy < 0 || y + cy >= gd.ny)
+                    BufIO<S>::template store<BUF_DEFAULT>(sv, plane, xo, ro);
+                if (y - cy < 0 || y - cy >= gd.ny) return;
             }
-            const int xd = int(wrap_back(uint32_t(x), L::c(i, 0), uint32_t(gd.nx)));
-            const int yd = int(wrap_back(uint32_t(y), L::c(i, 1), uint32_t(gd.ny)));
-            const int zd =
-                (L::D == 3) ? int(wrap_back(uint32_t(z), L::c(i, 2), uint32_t(gd.nz))) : 0;
-            const int64_t dst = (int64_t(zd) * gd.ny + yd) * gd.px + xd;
-            A[int64_t(i) * gd.P + dst] = sv;
+            BufIO<S>::template store<BUF_DEFAULT>(sv, plane, at.xs[cx + 3], at.row(cy, cz));
         };
-        put(std::integral_constant<int, ip>{}, ev + od);
-        if constexpr (im >= 0) put(std::integral_constant<int, im>{}, ev - od);
+        put(IP, ev + od);
+        if constexpr (decltype(IM)::value >= 0) put(IM, ev - od);
     });
 }
 
 // ---------------------------------------------------------------------------
 // K3: physical moments rho, u + g/2, theta of the state
 // ---------------------------------------------------------------------------
-template <int LAT, class S>
+template <int LAT, class S, bool WALLS>
 __global__ void __launch_bounds__(256)
     moments_kernel(const S *__restrict__ A, double *__restrict__ rho, double *__restrict__ u,
                    double *__restrict__ theta, GridDims gd, ForceDesc fd, StepCoef co,
@@ -704,13 +712,12 @@ __global__ void __launch_bounds__(256)
     using L = Lattice<LAT>;
     using T = typename ArithOf<S>::type;
     using C = Codec<L, S>;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= gd.nx) return;
+    int x, y, z;
+    if (!wave_cell(gd, block_wave(), x, y, z)) return;
     const int64_t N = gd.N;
     const int64_t cell = (int64_t(z) * gd.ny + y) * gd.nx + x;
     T h[L::Q];  // as stored (scaled for F16): raw_sums takes the scale out
-    gather_state<L, S, T>(A, gd, x, y, z, h, wd, co.rho0);
+    gather<L, S, T, WALLS>(A, gd, x, y, z, h, &wd, co.rho0);
     T g[3];
     load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
     const RawSums<T> rs = raw_sums<L, T, C>(h);
@@ -732,7 +739,7 @@ __global__ void __launch_bounds__(256)
 // For N = 2 the equilibrium's own part is added, sum_i f0_i |c_i|^2 c_i =
 // -rho u (D + 2 + |u|^2) (the rule's moments to degree 3) + sum_i (f0 - w rho)_i |c_i|^2 c_i.
 // ---------------------------------------------------------------------------
-template <int LAT, class S, int EQ, int FO>
+template <int LAT, class S, int EQ, int FO, bool WALLS>
 __global__ void __launch_bounds__(256)
     heatflux_kernel(const S *__restrict__ A, double *__restrict__ q, GridDims gd, ForceDesc fd,
                     StepCoef co, WallDesc wd)
@@ -740,13 +747,12 @@ __global__ void __launch_bounds__(256)
     using L = Lattice<LAT>;
     using T = typename ArithOf<S>::type;
     using C = Codec<L, S>;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y, z = blockIdx.z;
-    if (x >= gd.nx) return;
+    int x, y, z;
+    if (!wave_cell(gd, block_wave(), x, y, z)) return;
     const int64_t N = gd.N;
     const int64_t cell = (int64_t(z) * gd.ny + y) * gd.nx + x;
     T h[L::Q];
-    gather_state<L, S, T>(A, gd, x, y, z, h, wd, co.rho0);
+    gather<L, S, T, WALLS>(A, gd, x, y, z, h, &wd, co.rho0);
     T g[3];
     load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
     const RawSums<T> rs = raw_sums<L, T, C>(h);

@@ -8,18 +8,38 @@
 
 namespace lbm {
 
-inline dim3 cell_grid(const GridDims &gd, int bx)
+// Launch shapes of the kernels off the step path, over the row wavefronts; lds limits
+// the blocks of a CU as in step_shape.
+struct FieldShape {
+    dim3 grid, block;
+    unsigned lds;
+};
+inline FieldShape field_shape(const GridDims &gd, unsigned threads, unsigned lds)
 {
-    return dim3(unsigned((gd.nx + bx - 1) / bx), unsigned(gd.ny), unsigned(gd.nz));
+    const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz, wpb = threads / 64;
+    return FieldShape{dim3(unsigned((waves + wpb - 1) / wpb)), dim3(threads), lds};
 }
-
-// Threads per block along x: the requested count, at most nx rounded up to a
-// whole wavefront.
-inline int block_for(const GridDims &gd, int want)
+// Reading kernels: 256 threads; the FP32 moments of large grids 12 wavefronts a CU
+// (D3Q39 256^3 603 us against 624; FP64 and F16 within 2% either way).
+template <int LAT, class S> inline FieldShape moments_shape(const GridDims &gd)
 {
-    const int b = want > 0 ? want : 256;
-    const int nx64 = ((gd.nx + 63) / 64) * 64;
-    return b < nx64 ? b : nx64;
+    const bool large = sizeof(S) == 4 && buffer_lines_bytes<LAT, S>(gd) >= STEP_LARGE_BYTES;
+    return field_shape(gd, 256, large ? STEP_LDS_PER_CU / 3 : 0u);
+}
+// Scattering kernels (their shifted rows' lines are completed by neighbouring
+// wavefronts, in the L2 of one XCD if one block holds the whole row): whole rows
+// while 8 wavefronts do (4 on small grids), and on large grids few enough blocks
+// that the lines are complete before they leave the L2.  us, against 256 threads:
+// D3Q39 FP32 160^3 159 / 211, 256^3 589 / 675; FP64 129x95x110 150 / 156, D2Q37
+// 1537x1021 129 / 137; F16 256^3 375 / 416.
+template <int LAT, class S> inline FieldShape scatter_shape(const GridDims &gd)
+{
+    const unsigned k = unsigned((gd.nx + 63) / 64);  // wavefronts a row
+    const unsigned most = int64_t(k) * gd.ny * gd.nz <= 4096 ? 4u : 8u;
+    const unsigned w = k <= most ? k * (most / k) : most;
+    const bool large = buffer_lines_bytes<LAT, S>(gd) >= STEP_LARGE_BYTES;
+    const unsigned per_cu = (sizeof(S) == 2 ? 16u : 12u) / w;
+    return field_shape(gd, 64 * w, large ? STEP_LDS_PER_CU / per_cu : 0u);
 }
 
 template <int LAT, class F> hipError_t with_eq_fo(int eq, int fo, F &&f)
@@ -49,6 +69,12 @@ template <class F> hipError_t with_wall_policy(Policy p, F &&f)
 {
     if (p == Policy::RESIDENT) return f(std::integral_constant<Policy, Policy::RESIDENT>{});
     return f(std::integral_constant<Policy, Policy::STREAM>{});
+}
+
+// f(std::bool_constant) for a handle with plates or without
+template <class F> hipError_t with_walls(const WallDesc &wd, F &&f)
+{
+    return wd.on ? f(std::true_type{}) : f(std::false_type{});
 }
 
 template <int LAT, class S>
@@ -125,12 +151,15 @@ hipError_t launch_init_ls(int eq, int fo, const double *rho, const double *u, co
                           void *A, const GridDims &gd, const ForceDesc &fd, const StepCoef &co,
                           const LaunchCfg &lc)
 {
-    const int bx = block_for(gd, 256);
+    const FieldShape sh = scatter_shape<LAT, S>(gd);
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
-        hipLaunchKernelGGL((init_kernel<LAT, S, decltype(E)::value, decltype(O)::value>),
-                           cell_grid(gd, bx), dim3(bx), 0, lc.stream, rho, u, theta,
-                           static_cast<S *>(A), gd, fd, co, lc.walls);
-        return hipGetLastError();
+        return with_walls(lc.walls, [&](auto W) {
+            hipLaunchKernelGGL((init_kernel<LAT, S, decltype(E)::value, decltype(O)::value,
+                                            decltype(W)::value>),
+                               sh.grid, sh.block, sh.lds, lc.stream, rho, u, theta,
+                               static_cast<S *>(A), gd, fd, co);
+            return hipGetLastError();
+        });
     });
 }
 
@@ -139,22 +168,28 @@ hipError_t launch_moments_ls(const void *A, double *rho, double *u, double *thet
                              const GridDims &gd, const ForceDesc &fd, const StepCoef &co,
                              const LaunchCfg &lc)
 {
-    const int bx = block_for(gd, 256);
-    hipLaunchKernelGGL((moments_kernel<LAT, S>), cell_grid(gd, bx), dim3(bx), 0, lc.stream,
-                       static_cast<const S *>(A), rho, u, theta, gd, fd, co, lc.walls);
-    return hipGetLastError();
+    const FieldShape sh = moments_shape<LAT, S>(gd);
+    return with_walls(lc.walls, [&](auto W) {
+        hipLaunchKernelGGL((moments_kernel<LAT, S, decltype(W)::value>), sh.grid, sh.block, sh.lds,
+                           lc.stream, static_cast<const S *>(A), rho, u,
+                           theta, gd, fd, co, lc.walls);
+        return hipGetLastError();
+    });
 }
 
 template <int LAT, class S>
 hipError_t launch_heat_flux_ls(int eq, int fo, const void *A, double *q, const GridDims &gd,
                                const ForceDesc &fd, const StepCoef &co, const LaunchCfg &lc)
 {
-    const int bx = block_for(gd, 256);
+    const FieldShape sh = field_shape(gd, 256, 0);
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
-        hipLaunchKernelGGL((heatflux_kernel<LAT, S, decltype(E)::value, decltype(O)::value>),
-                           cell_grid(gd, bx), dim3(bx), 0, lc.stream, static_cast<const S *>(A),
-                           q, gd, fd, co, lc.walls);
-        return hipGetLastError();
+        return with_walls(lc.walls, [&](auto W) {
+            hipLaunchKernelGGL((heatflux_kernel<LAT, S, decltype(E)::value, decltype(O)::value,
+                                                decltype(W)::value>),
+                               sh.grid, sh.block, sh.lds, lc.stream,
+                               static_cast<const S *>(A), q, gd, fd, co, lc.walls);
+            return hipGetLastError();
+        });
     });
 }
 
