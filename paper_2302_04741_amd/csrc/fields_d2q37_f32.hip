@@ -6,6 +6,9 @@ template hipError_t launch_init_ls<0, float>(int, int, const double *, const dou
                                                const double *, void *, const GridDims &,
                                                const ForceDesc &, const StepCoef &,
                                                const LaunchCfg &);
+template hipError_t launch_rebuild_ls<0, float>(int, int, const void *, void *, const GridDims &,
+                                              const ForceDesc &, const ForceDesc &,
+                                              const StepCoef &, const LaunchCfg &);
 template hipError_t launch_moments_ls<0, float>(const void *, double *, double *, double *,
                                                   const GridDims &, const ForceDesc &,
                                                   const StepCoef &, const LaunchCfg &);

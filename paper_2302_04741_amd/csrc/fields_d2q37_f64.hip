@@ -6,6 +6,9 @@ template hipError_t launch_init_ls<0, double>(int, int, const double *, const do
                                                const double *, void *, const GridDims &,
                                                const ForceDesc &, const StepCoef &,
                                                const LaunchCfg &);
+template hipError_t launch_rebuild_ls<0, double>(int, int, const void *, void *, const GridDims &,
+                                              const ForceDesc &, const ForceDesc &,
+                                              const StepCoef &, const LaunchCfg &);
 template hipError_t launch_moments_ls<0, double>(const void *, double *, double *, double *,
                                                   const GridDims &, const ForceDesc &,
                                                   const StepCoef &, const LaunchCfg &);

@@ -7,6 +7,9 @@ template hipError_t launch_init_ls<1, __half>(int, int, const double *, const do
                                                const double *, void *, const GridDims &,
                                                const ForceDesc &, const StepCoef &,
                                                const LaunchCfg &);
+template hipError_t launch_rebuild_ls<1, __half>(int, int, const void *, void *, const GridDims &,
+                                              const ForceDesc &, const ForceDesc &,
+                                              const StepCoef &, const LaunchCfg &);
 template hipError_t launch_moments_ls<1, __half>(const void *, double *, double *, double *,
                                                   const GridDims &, const ForceDesc &,
                                                   const StepCoef &, const LaunchCfg &);

@@ -181,6 +181,17 @@ lbm_status check_params(const lbm_params *p)
     return LBM_OK;
 }
 
+// Whether work on the stream is being captured (or cannot be told not to be).
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 // Whether a kernel on the current device can address p: memory of this device.
 bool on_this_device(const void *p)
 {
@@ -386,6 +397,24 @@ lbm_status lbm_set_force(lbm_sim *s, int32_t kind, const double *g, int32_t axis
         return fail(LBM_ENOSPACE, "force table does not fit the workspace");
 
     hipError_t e;
+    if (s->step == 0 && s->fd.kind == 0 && !s->wd.on && !capturing(s->stream)) {
+        // Rebuild f~ = f0 - F/2 for the new force in one pass into the idle
+        // buffer.  Only where the old force is uniform (in the launch arguments:
+        // the table then belongs to the new one already), without plates, and not
+        // into a graph (whose replays would start from the other buffer): the rest
+        // goes the general way below, in place.
+        if (count > 0) {
+            e = launch_convert(s->p.storage, g, s->gtab, count, s->stream);
+            if (e != hipSuccess) return dev_fail(e, "force table conversion");
+        }
+        e = launch_rebuild(s->p.lattice, s->p.storage, s->eq, s->p.force_order, s->pop[s->cur],
+                           s->pop[s->cur ^ 1], s->gd, s->fd, nf, s->co, cfg(s));
+        if (e != hipSuccess) return dev_fail(e, "rebuild kernel launch");
+        s->cur ^= 1;
+        s->fd = nf;
+        s->gen++;
+        return ok();
+    }
     void *scratch = s->pop[s->cur ^ 1];
     double *mrho = static_cast<double *>(scratch);
     double *mu = mrho + s->N;

@@ -100,6 +100,15 @@ hipError_t launch_init(int lat, int storage, int eq, int fo, const double *rho, 
 #undef LBM_INIT
 }
 
+hipError_t launch_rebuild(int lat, int storage, int eq, int fo, const void *A, void *B,
+                          const GridDims &gd, const ForceDesc &old_force, const ForceDesc &force,
+                          const StepCoef &co, const LaunchCfg &lc)
+{
+#define LBM_RB(L, S) launch_rebuild_ls<L, S>(eq, fo, A, B, gd, old_force, force, co, lc)
+    LBM_BY_STORAGE(LBM_RB);
+#undef LBM_RB
+}
+
 hipError_t launch_moments(int lat, int storage, const void *A, double *rho, double *u,
                           double *theta, const GridDims &gd, const ForceDesc &fd,
                           const StepCoef &co, const LaunchCfg &lc)

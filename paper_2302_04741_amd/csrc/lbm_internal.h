@@ -773,6 +773,9 @@ hipError_t launch_step(int lat, int storage, int eq, int fo, const void *A, void
 hipError_t launch_init(int lat, int storage, int eq, int fo, const double *rho, const double *u,
                        const double *theta, void *A, const GridDims &gd, const ForceDesc &fd,
                        const StepCoef &co, const LaunchCfg &lc);
+hipError_t launch_rebuild(int lat, int storage, int eq, int fo, const void *A, void *B,
+                          const GridDims &gd, const ForceDesc &old_force, const ForceDesc &force,
+                          const StepCoef &co, const LaunchCfg &lc);
 hipError_t launch_moments(int lat, int storage, const void *A, double *rho, double *u,
                           double *theta, const GridDims &gd, const ForceDesc &fd,
                           const StepCoef &co, const LaunchCfg &lc);
@@ -833,6 +836,10 @@ template <int LAT, class S>
 hipError_t launch_init_ls(int eq, int fo, const double *rho, const double *u, const double *theta,
                           void *A, const GridDims &gd, const ForceDesc &fd, const StepCoef &co,
                           const LaunchCfg &lc);
+template <int LAT, class S>
+hipError_t launch_rebuild_ls(int eq, int fo, const void *A, void *B, const GridDims &gd,
+                             const ForceDesc &old_force, const ForceDesc &force,
+                             const StepCoef &co, const LaunchCfg &lc);
 template <int LAT, class S>
 hipError_t launch_moments_ls(const void *A, double *rho, double *u, double *theta,
                              const GridDims &gd, const ForceDesc &fd, const StepCoef &co,

@@ -646,31 +646,11 @@ __global__ void __launch_bounds__(256)
 // (write-back) stores, since lines are completed by neighbouring wavefronts
 // (streamed or written through they cost 20-120% more).
 // ---------------------------------------------------------------------------
-template <int LAT, class S, int EQ, int FO, bool WALLS>
-__global__ void __launch_bounds__(512)
-    init_kernel(const double *__restrict__ rho, const double *__restrict__ u,
-                const double *__restrict__ theta, S *__restrict__ A, GridDims gd, ForceDesc fd,
-                StepCoef co)
+template <class L, class S, class T, int EQ, int FO, bool WALLS>
+__device__ __forceinline__ void scatter_initial(const CellState<T> &cs, S *__restrict__ A,
+                                                const GridDims &gd, int x, int y, int z)
 {
-    using L = Lattice<LAT>;
-    using T = typename ArithOf<S>::type;
-    int x, y, z;
-    if (!wave_cell(gd, block_wave(), x, y, z)) return;
-    const int64_t N = gd.N;
     const int64_t row = int64_t(z) * gd.ny + y;
-    const int64_t cell = row * gd.nx + x;
-
-    T g[3];
-    load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
-    CellState<T> cs;
-    cs.rho = T(rho[cell]);
-    cs.drho = T(rho[cell] - co.rho0);  // the deviation rounded once
-    cs.th = T(theta[cell]);
-    for (int a = 0; a < 3; ++a) {
-        cs.ub[a] = (a < L::D) ? T(u[int64_t(a) * N + cell]) : T(0);
-        cs.g[a] = g[a];
-        for (int b = 0; b < 3; ++b) cs.sig[a][b] = T(0);
-    }
     // the slot the first step pulls velocity i of this cell from is x - c_i
     const PullOffsets<L, S> at(gd, x, y, z, true);
     const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
@@ -698,6 +678,68 @@ __global__ void __launch_bounds__(512)
         put(IP, ev + od);
         if constexpr (decltype(IM)::value >= 0) put(IM, ev - od);
     });
+}
+
+template <int LAT, class S, int EQ, int FO, bool WALLS>
+__global__ void __launch_bounds__(512)
+    init_kernel(const double *__restrict__ rho, const double *__restrict__ u,
+                const double *__restrict__ theta, S *__restrict__ A, GridDims gd, ForceDesc fd,
+                StepCoef co)
+{
+    using L = Lattice<LAT>;
+    using T = typename ArithOf<S>::type;
+    int x, y, z;
+    if (!wave_cell(gd, block_wave(), x, y, z)) return;
+    const int64_t N = gd.N;
+    const int64_t cell = (int64_t(z) * gd.ny + y) * gd.nx + x;
+
+    T g[3];
+    load_force<T, T, L::D>(fd, gd, x, y, z, cell, g);
+    CellState<T> cs;
+    cs.rho = T(rho[cell]);
+    cs.drho = T(rho[cell] - co.rho0);  // the deviation rounded once
+    cs.th = T(theta[cell]);
+    for (int a = 0; a < 3; ++a) {
+        cs.ub[a] = (a < L::D) ? T(u[int64_t(a) * N + cell]) : T(0);
+        cs.g[a] = g[a];
+        for (int b = 0; b < 3; ++b) cs.sig[a][b] = T(0);
+    }
+    scatter_initial<L, S, T, EQ, FO, WALLS>(cs, A, gd, x, y, z);
+}
+
+// K2b: the state rebuilt for another force before the first step, in one pass: the
+// moments of the state in A under the old force, f~ = f0 - F/2 with the new one
+// scattered into B.  Through FP64 fields in between (K3, then K2) it moves 80 bytes a
+// cell more: D3Q39 FP32 160^3 314 us, in one pass 259 (256^3: 1213 / 980).  The
+// values are the same: K3
+// writes T widened to FP64, K2 narrows it back.
+template <int LAT, class S, int EQ, int FO>
+__global__ void __launch_bounds__(512)
+    rebuild_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd, ForceDesc old_force,
+                   ForceDesc force, StepCoef co, uint32_t *ctr, int cur)
+{
+    using L = Lattice<LAT>;
+    using T = typename ArithOf<S>::type;
+    using C = Codec<L, S>;
+    const uint32_t wave = block_wave();
+    // the step number goes with the state
+    if (C::STOCHASTIC && wave == 0 && threadIdx.x == 0) ctr[cur ^ 1] = ctr[cur];
+    int x, y, z;
+    if (!wave_cell(gd, wave, x, y, z)) return;
+    const int64_t cell = (int64_t(z) * gd.ny + y) * gd.nx + x;
+    CellState<T> cs;
+    {
+        T h[L::Q], g[3];
+        gather<L, S, T>(A, gd, x, y, z, h);
+        load_force<T, T, L::D>(old_force, gd, x, y, z, cell, g);
+        const RawSums<T> rs = raw_sums<L, T, C>(h);
+        finish_moments<L, T, false>(rs, g, co, cs);
+    }
+    T g[3];
+    load_force<T, T, L::D>(force, gd, x, y, z, cell, g);
+    cs.drho = T(double(cs.rho) - co.rho0);
+    for (int a = 0; a < 3; ++a) cs.g[a] = g[a];
+    scatter_initial<L, S, T, EQ, FO, false>(cs, B, gd, x, y, z);
 }
 
 // ---------------------------------------------------------------------------

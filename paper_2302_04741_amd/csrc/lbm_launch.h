@@ -164,6 +164,20 @@ hipError_t launch_init_ls(int eq, int fo, const double *rho, const double *u, co
 }
 
 template <int LAT, class S>
+hipError_t launch_rebuild_ls(int eq, int fo, const void *A, void *B, const GridDims &gd,
+                             const ForceDesc &old_force, const ForceDesc &force,
+                             const StepCoef &co, const LaunchCfg &lc)
+{
+    const FieldShape sh = scatter_shape<LAT, S>(gd);
+    return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
+        hipLaunchKernelGGL((rebuild_kernel<LAT, S, decltype(E)::value, decltype(O)::value>),
+                           sh.grid, sh.block, sh.lds, lc.stream, static_cast<const S *>(A),
+                           static_cast<S *>(B), gd, old_force, force, co, lc.ctr, lc.cur);
+        return hipGetLastError();
+    });
+}
+
+template <int LAT, class S>
 hipError_t launch_moments_ls(const void *A, double *rho, double *u, double *theta,
                              const GridDims &gd, const ForceDesc &fd, const StepCoef &co,
                              const LaunchCfg &lc)

@@ -37,6 +37,10 @@ def test_initial_moments_are_the_inputs(lattice, dims, storage):
     check()
     s.set_force(wl.force[1])     # rebuilds the state with the force
     check()
-    s.set_force([0.0] * len(wl.force[1]))
+    prof = torch.ones((s.D, s.dims[1]), dtype=torch.float64)
+    s.set_force(axis=1, profile=prof * torch.as_tensor(wl.force[1])[:, None])
     check()
+    s.set_force([0.0] * len(wl.force[1]))  # from a table: through the fields
+    check()
+    assert s.step_count == 0
     s.close()
