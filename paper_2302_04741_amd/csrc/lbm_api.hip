@@ -205,18 +205,20 @@ bool on_this_device(const void *p)
 }
 
 // The dense planes out of the handle's current buffer (exporting) or into it.
-// Rows that are not whole 64-value runs go through the row kernel, whose 16-byte
-// lanes take half the time of the runtime's 2-D copy there (D2Q37 1017^2 FP32 54
-// us against 107); where the rows have no padding that copy is one contiguous
-// run at full rate (6.1 TB/s on D3Q39 256^3 F16), and it takes what the kernel
-// cannot: memory of another device, or not aligned to the stored type.  Small
-// states keep it too: either way they take a launch, and the pointer query of the
-// kernel's path costs the host 0.5 us.
-constexpr size_t ROW_KERNEL_MIN_BYTES = size_t(2) << 20;
+// The runtime's 2-D copy is at its best on rows of whole 16-byte units and 1 KiB and
+// more (D2Q37 2000x1100 FP64 234 us against the row kernel's 241; where rows have no
+// padding it is one contiguous run, 6.1 TB/s) and falls to 1-3 TB/s on others, where
+// the row kernel keeps 3-6 TB/s (D2Q37 1017^2 FP32 49 us against 108).  Small states
+// keep it too (130^2 FP32, 2.5 MB: 3.5 us against 4.1), and it takes what the kernel
+// cannot: memory of another device, or not aligned to the stored type.
+constexpr size_t ROW_KERNEL_MIN_BYTES = size_t(6) << 20;
+
 hipError_t copy_populations(const lbm_sim *s, void *dense, bool exporting)
 {
     const size_t sb = storage_bytes(s->p.storage);
-    if (s->gd.px != s->gd.nx && lbm_population_bytes(s) >= ROW_KERNEL_MIN_BYTES &&
+    const size_t row = size_t(s->gd.nx) * sb;
+    if (s->gd.px != s->gd.nx && (row % 16 != 0 || row < 1024) &&
+        lbm_population_bytes(s) >= ROW_KERNEL_MIN_BYTES &&
         reinterpret_cast<uintptr_t>(dense) % sb == 0 && on_this_device(dense))
         return launch_copy_rows(s->p.storage, s->pop[s->cur], dense, s->gd, s->Q, exporting,
                                 s->stream);
