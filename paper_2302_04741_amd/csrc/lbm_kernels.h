@@ -288,7 +288,9 @@ struct StepShape {
 // wavefronts against as many as the registers allow (256 threads): D3Q39 160^3
 // 227 / 234, 224^3 614 / 657, 256^3 913 / 957 (1024 threads, 16 wavefronts: 942),
 // D2Q37 2048^2 220 / 226, 3000^2 475 / 500; below that size it gains or loses 2%,
-// and F16, with half the bytes a wavefront, loses (256^3 700 / 496).
+// and F16, with half the bytes a wavefront, loses (256^3 700 / 496); F16 of 1 GiB a
+// buffer and more takes 512 threads unlimited (256^3 476 / 490, D2Q37 4096^2 441 /
+// 458; below it is within 2% either way).
 constexpr int64_t MIB = int64_t(1) << 20;
 constexpr int64_t STEP_CACHED_BYTES = 128 * MIB;  // two such buffers fit the memory-side cache
 constexpr int64_t STEP_LARGE_BYTES = 400 * MIB;
@@ -329,7 +331,8 @@ inline StepShape step_shape(int64_t buffer_bytes, int64_t waves, int threads)
     const bool large = sizeof(S) == 4 && buffer_bytes >= STEP_LARGE_BYTES;
     int bx = threads;
     if (bx <= 0 && buffer_bytes <= STEP_CACHED_BYTES) bx = small_grid_threads<LAT, S>(waves);
-    if (bx <= 0) bx = sizeof(S) == 8 ? 128 : (large ? 512 : 256);
+    const bool wide = large || (sizeof(S) == 2 && buffer_bytes >= 1024 * MIB);
+    if (bx <= 0) bx = sizeof(S) == 8 ? 128 : (wide ? 512 : 256);
     bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
     const bool limit = large && (bx == 256 || bx == 512);
     return StepShape{bx, limit ? STEP_LDS_PER_CU * unsigned(bx) / 512u : 0u};
