@@ -118,6 +118,49 @@ def request_bytes(req: Request, storage: str) -> int:
     return _lib.workspace_bytes(p) + 256
 
 
+class _HostCopy:
+    """Device tensors into ordinary host memory through two pinned buffers.
+
+    A kept result is a fresh host allocation of up to hundreds of MB.  Tensor.cpu()
+    lets the driver fault it in page by page (60 MB: 15 ms, 4 GB/s).  Here the
+    memory comes from numpy (huge pages) and is filled by the CPU from one pinned
+    buffer while the next piece arrives in the other (2.1 ms, 30 GB/s).  The result
+    is pageable, as before; the 16 MB of pinned memory live as long as the run.
+    """
+
+    PIECE = 8 << 20
+
+    def __init__(self):
+        self.stage = None
+
+    def __call__(self, src):
+        """`src` (a uint8 device tensor, ready on the current stream) as a CPU tensor."""
+        import torch
+
+        out = torch.from_numpy(np.empty(src.numel(), dtype=np.uint8))
+        if self.stage is None:
+            self.stage = [(torch.empty(self.PIECE, dtype=torch.uint8, pin_memory=True),
+                           torch.cuda.Event()) for _ in range(2)]
+        pieces = [(o, min(self.PIECE, src.numel() - o))
+                  for o in range(0, src.numel(), self.PIECE)]
+
+        def fetch(k):
+            buf, ev = self.stage[k & 1]
+            o, n = pieces[k]
+            buf[:n].copy_(src[o:o + n], non_blocking=True)
+            ev.record()
+
+        if pieces:
+            fetch(0)
+        for k, (o, n) in enumerate(pieces):
+            if k + 1 < len(pieces):
+                fetch(k + 1)  # the other buffer: its last piece was taken out already
+            buf, ev = self.stage[k & 1]
+            ev.synchronize()
+            out[o:o + n].copy_(buf[:n])
+        return out
+
+
 class Server:
     """Continuous batching on one dedicated stream, pipelined with the host.
 
@@ -197,6 +240,7 @@ class Server:
         max_active = 0
         chunks = 0
         slot = 0
+        to_host = _HostCopy()
 
         def now():
             return time.perf_counter() - t0
@@ -206,7 +250,7 @@ class Server:
             pops = None
             if self.keep(r.rid) and not err:
                 with torch.cuda.stream(stream):
-                    pops = a["sim"].get_populations().cpu()
+                    pops = to_host(a["sim"].get_populations())
             results.append(Result(r.rid, r.arrival if realtime else 0.0, a["admitted"], now(),
                                   r.workload.ncell, a["planned"], not err, err,
                                   a.get("totals"), pops, a["admitted_chunk"]))

@@ -28,8 +28,11 @@ def _as_device(torch, a, shape, device, stream, keep):
     if isinstance(a, torch.Tensor) and a.is_cuda:
         t = a.to(device=device, dtype=torch.float64).reshape(shape).contiguous()
     else:
-        arr = np.ascontiguousarray(np.broadcast_to(np.asarray(a, dtype=np.float64), shape))
-        t = torch.from_numpy(arr.copy()).to(device=device, non_blocking=False)
+        arr = np.asarray(a, dtype=np.float64)
+        if arr.shape != tuple(shape) or not (arr.flags.c_contiguous and arr.flags.writeable):
+            arr = np.ascontiguousarray(np.broadcast_to(arr, shape)).copy()
+        # (a blocking copy: the caller's array is read before this returns)
+        t = torch.from_numpy(arr).to(device=device, non_blocking=False)
     # read on `stream`: keep the memory from being reused before that stream
     # has used it (the caller's tensor itself, or a temporary made here)
     t.record_stream(stream)
