@@ -59,32 +59,37 @@ constexpr int BUF_DEFAULT = 0, BUF_NT = 2, BUF_THROUGH = 17, BUF_STREAM = 18;
 // written once a step, and what one step writes is what the next one reads, so
 // the 256 MB memory-side cache can serve part of a step's reads where the stores
 // leave their lines in it.  T: bytes of one population buffer, whole 128-byte
-// lines.  us a step, by policy (FP32 unless noted):
-//                            RESIDENT  KEEP_WRITES  STREAM   (nt stores alone)
-//   D2Q37 512^2    T 39 MB     14.8       18.2       18.2       18.2
-//   D2Q37 900^2    T 124 MB    38.7       47.6       46.5       46.4
-//   D3Q39 96^3 F16 T 71 MB     26.4       40.7       41.1       39.7
-//   D3Q39 96^3     T 138 MB    51.5       45.7       53         55.1
-//   D3Q39 128^3    T 327 MB   127        110.6      122        127.6
-//   D2Q37 1024^2 FP64 310 MB  128        105.5      117        125.3
-//   D3Q39 144^3    T 466 MB                         181.9      186.9
-//   D3Q39 256^3 FP64 5.2 GB  1902       1886       1825       1889
-// RESIDENT: both buffers fit: default loads, stores written through (written back
-// by default they cost the same, but leave the L2's dirty lines to the end of the
-// launch).  KEEP_WRITES: one buffer fits about: loads marked nt leave the cache
-// to what is being written.  STREAM: neither: stores streamed.
-// Reversed: odd steps sweep the grid backwards, so that a step first reads what
-// the last one wrote last; it pays once T exceeds half the cache.
-enum class Policy { RESIDENT, KEEP_WRITES, STREAM };
+// lines.
+//
+// RESIDENT (both buffers fit): default loads, stores written through (written back
+//   by default they cost the same, but leave the L2's dirty lines to the end of
+//   the launch).
+// STREAM (larger): stores streamed past the cache, except the last W bytes of a
+//   sweep, which are written through (KEEP); the next step sweeps the other way
+//   and reads those first.  Loads of the kept part are marked nt, so that what is
+//   being kept is not displaced by what is being read.
+// STREAM_NT: STREAM with every load nt.
+//
+// us a step, STREAM against every store nt (the rest as here):
+//   D2Q37 FP32 1024^2 (T 155 MB) 52.5 / 62.7, 1200^2 (219) 70 / 81, 1400^2 (308) 100 /
+//   107, 2048^2 (621) 207 / 220, 3000^2 (1332) 462 / 476; FP64 900^2 (248) 77 / 88,
+//   1537x1021 (465) 165 / 179; F16 1800^2 (250) 83 / 91, D3Q39 256^3 (1309) 471 / 484;
+//   D3Q39 FP32 120^3 (288) 100 / 118, 160^3 (639) 230 / 239, 256^3 (2617) 940 / 948.
+// RESIDENT against the same: D2Q37 FP32 512^2 (39) 14.7 / 18.0, 900^2 (124) 39 / 46;
+//   D3Q39 F16 96^3 (71) 26 / 40.
+enum class Policy { RESIDENT, STREAM, STREAM_NT, KEEP };
 template <Policy P> struct CacheBits;
 template <> struct CacheBits<Policy::RESIDENT> {
     static constexpr int load = BUF_DEFAULT, store = BUF_THROUGH;
 };
-template <> struct CacheBits<Policy::KEEP_WRITES> {
-    static constexpr int load = BUF_NT, store = BUF_THROUGH;
-};
 template <> struct CacheBits<Policy::STREAM> {
     static constexpr int load = BUF_DEFAULT, store = BUF_STREAM;
+};
+template <> struct CacheBits<Policy::STREAM_NT> {
+    static constexpr int load = BUF_NT, store = BUF_STREAM;
+};
+template <> struct CacheBits<Policy::KEEP> {
+    static constexpr int load = BUF_NT, store = BUF_THROUGH;
 };
 
 typedef int RsrcWords __attribute__((ext_vector_type(4)));

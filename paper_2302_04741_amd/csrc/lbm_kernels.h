@@ -18,6 +18,8 @@
 // grid element of B exactly once, at the thread's own cell.
 #pragma once
 
+#include <algorithm>
+
 #include "lbm_internal.h"
 
 namespace lbm {
@@ -339,27 +341,28 @@ inline StepShape step_shape(int64_t buffer_bytes, int64_t waves, int threads)
 }
 
 // Cache policy for a population buffer of T bytes (whole lines), measured from
-// T = 10 MB to 5 GB (table at Policy).  Both buffers fit the memory-side cache up
-// to 128 MiB each.  Past it, up to 400 MiB, KEEP_WRITES gains 3-18% on D3Q39 (F16:
-// to 200 MiB; past that its loads of half a line a wavefront lose 10% with nt) and
-// on D2Q37 from 240 MiB; D2Q37 below that re-reads the lines at its blocks' row
-// ends (a block is a quarter of a row) and wants default loads: up to 192 MiB
-// RESIDENT swept backwards still gains 3-8%, between 192 and 240 MiB and for F16
-// nothing gains.
+// T = 10 MB to 5 GB.  Both buffers fit the memory-side cache up to 128 MiB each.
+// Past it the kept part W is what the cache holds beside the traffic: measured best
+// between 0.5 and 0.6 T up to T = 300 MB, and flat from 160 to 240 MB above.  D3Q39
+// FP64 between 250 and 700 MB gains from nt loads throughout and W = 240 MB
+// (129x95x110 170 us against 178, 116^3 180 / 191, 126^3 225 / 228; 136^3, 785 MB,
+// loses, 306 / 303; the others lose everywhere).
 struct StepPolicy {
     Policy policy;
-    bool reversed;  // odd steps sweep backwards
+    double keep;  // share of the sweep, at its end, whose stores are kept; 0: no reversal
 };
 template <int LAT, class S> inline StepPolicy step_policy(int64_t T)
 {
-    if (T <= STEP_CACHED_BYTES) return {Policy::RESIDENT, false};
-    if (LAT == 1) {
-        if (T <= (sizeof(S) == 2 ? 200 : 400) * MIB) return {Policy::KEEP_WRITES, true};
-    } else if (sizeof(S) > 2) {
-        if (T <= 192 * MIB) return {Policy::RESIDENT, true};
-        if (T > 240 * MIB && T <= 400 * MIB) return {Policy::KEEP_WRITES, true};
-    }
-    return {Policy::STREAM, true};
+    if (T <= STEP_CACHED_BYTES) return {Policy::RESIDENT, 0.0};
+    const double t = double(T);
+    if (LAT == 1 && sizeof(S) == 8 && t > 250e6 && t <= 700e6)
+        return {Policy::STREAM_NT, std::min(0.57, 240e6 / t)};
+    return {Policy::STREAM, std::min(0.55, 200e6 / t)};
+}
+// First of n work items, in the order of the sweep, whose stores are kept.
+inline int64_t keep_from(const StepPolicy &sp, int64_t n)
+{
+    return n - int64_t(double(n) * sp.keep);
 }
 // Bytes of one population buffer in whole 128-byte lines.
 template <int LAT, class S> inline int64_t buffer_lines_bytes(const GridDims &gd)
@@ -506,7 +509,12 @@ __device__ __forceinline__ uint32_t block_wave()
 // schedule takes 170).
 template <class S> constexpr int step_min_waves() { return sizeof(S) == 8 ? 3 : 5; }
 
-// The block's place in the sweep: the reversed sweep of odd steps (see Policy).
+// Between two inlined cell updates: left to itself the compiler forms the scalars of
+// both before the branch between them, more than the scalar registers hold (106 used
+// and spilled against 55).
+__device__ __forceinline__ void keep_apart() { asm volatile("" ::: "memory"); }
+
+// The block's place on the grid: odd steps sweep it backwards (see Policy).
 __device__ __forceinline__ uint32_t swept_block(int backwards)
 {
     return backwards ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
@@ -516,7 +524,7 @@ template <int LAT, class S, int EQ, int FO, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     __attribute__((amdgpu_waves_per_eu(step_min_waves<S>(), 8)))
     step_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd, ForceDesc fd,
-                StepCoef co, uint32_t *ctr, int cur, int backwards)
+                StepCoef co, uint32_t *ctr, int cur, int backwards, uint32_t keep)
 {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(
         swept_block(backwards) * (blockDim.x >> 6) + (threadIdx.x >> 6));
@@ -524,7 +532,13 @@ __global__ void __launch_bounds__(step_max_threads<S>())
     advance_step_number<S>(ctr, cur, step, wave == 0 && threadIdx.x == 0);
     int x, y, z;
     if (!wave_cell(gd, wave, x, y, z)) return;
-    step_cell<LAT, S, EQ, FO, P>(A, B, gd, fd, co, x, y, z, step);
+    if (P != Policy::RESIDENT && blockIdx.x >= keep) {  // the sweep's last blocks (see Policy)
+        keep_apart();
+        step_cell<LAT, S, EQ, FO, P == Policy::RESIDENT ? P : Policy::KEEP>(A, B, gd, fd, co, x, y,
+                                                                            z, step);
+    } else {
+        step_cell<LAT, S, EQ, FO, P>(A, B, gd, fd, co, x, y, z, step);
+    }
 }
 
 // K7 (diagnostic): the memory traffic of K1 alone -- every population read
@@ -589,7 +603,7 @@ __global__ void __launch_bounds__(step_max_threads<S>())
 template <int LAT, class S, int EQ, int FO, Policy P, bool WALLS>
 __global__ void __launch_bounds__(256)
     multi_step_kernel(const int64_t *__restrict__ begin, const TileSim *__restrict__ sims,
-                      int nsims, int64_t ntiles, int parity, int backwards)
+                      int nsims, int64_t ntiles, int parity, int backwards, int64_t keep)
 {
     const int64_t nw = int64_t(gridDim.x) * (blockDim.x >> 6);
     int64_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
@@ -628,7 +642,13 @@ __global__ void __launch_bounds__(256)
                 continue;
             }
         }
-        step_cell<LAT, S, EQ, FO, P>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step);
+        if (!WALLS && P != Policy::RESIDENT && w >= keep) {  // the sweep's last tiles
+            keep_apart();
+            step_cell<LAT, S, EQ, FO, WALLS || P == Policy::RESIDENT ? P : Policy::KEEP>(
+                A, B, sd.gd, sd.fd, sd.co, x, y, z, step);
+        } else {
+            step_cell<LAT, S, EQ, FO, P>(A, B, sd.gd, sd.fd, sd.co, x, y, z, step);
+        }
     }
 }
 

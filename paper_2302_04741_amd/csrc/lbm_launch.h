@@ -53,18 +53,17 @@ template <int LAT, class F> hipError_t with_eq_fo(int eq, int fo, F &&f)
     return r;
 }
 
-// f(policy constant) for a runtime policy
-template <class F> hipError_t with_policy(Policy p, F &&f)
+// f(policy constant) for a runtime policy (STREAM_NT serves D3Q39 FP64 only)
+template <int LAT, class S, class F> hipError_t with_policy(Policy p, F &&f)
 {
-    switch (p) {
-    case Policy::RESIDENT: return f(std::integral_constant<Policy, Policy::RESIDENT>{});
-    case Policy::KEEP_WRITES: return f(std::integral_constant<Policy, Policy::KEEP_WRITES>{});
-    default: return f(std::integral_constant<Policy, Policy::STREAM>{});
+    if (p == Policy::RESIDENT) return f(std::integral_constant<Policy, Policy::RESIDENT>{});
+    if constexpr (LAT == 1 && sizeof(S) == 8) {
+        if (p == Policy::STREAM_NT) return f(std::integral_constant<Policy, Policy::STREAM_NT>{});
     }
+    return f(std::integral_constant<Policy, Policy::STREAM>{});
 }
-
-// The same for the kernels with plates, which come in two of them: channels are
-// small or, like their periodic neighbours in size, streamed.
+// The same for the kernels with plates, whose larger grids stream every store, in
+// one direction (channels are small).
 template <class F> hipError_t with_wall_policy(Policy p, F &&f)
 {
     if (p == Policy::RESIDENT) return f(std::integral_constant<Policy, Policy::RESIDENT>{});
@@ -89,12 +88,13 @@ hipError_t launch_step_ls(int eq, int fo, const void *A, void *B, const GridDims
     const int64_t wpb = sh.threads / 64;
     const dim3 grid(unsigned((waves + wpb - 1) / wpb));
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
-        return with_policy(sp.policy, [&](auto P) {
+        return with_policy<LAT, S>(sp.policy, [&](auto P) {
             hipLaunchKernelGGL((step_kernel<LAT, S, decltype(E)::value, decltype(O)::value,
                                             decltype(P)::value>),
                                grid, dim3(sh.threads), sh.lds, lc.stream,
                                static_cast<const S *>(A), static_cast<S *>(B), gd, fd, co, lc.ctr,
-                               lc.cur, int(sp.reversed && lc.cur));
+                               lc.cur, int(sp.keep > 0 && lc.cur),
+                               uint32_t(keep_from(sp, grid.x)));
             return hipGetLastError();
         });
     });
@@ -108,7 +108,7 @@ hipError_t launch_pattern_ls(const void *A, void *B, const GridDims &gd, const L
     const int64_t bytes = buffer_lines_bytes<LAT, S>(gd);
     const StepShape sh = step_shape<LAT, S>(bytes, waves, lc.block);
     const int64_t wpb = sh.threads / 64;
-    return with_policy(step_policy<LAT, S>(bytes).policy, [&](auto P) {
+    return with_policy<LAT, S>(step_policy<LAT, S>(bytes).policy, [&](auto P) {
         hipLaunchKernelGGL((pattern_kernel<LAT, S, decltype(P)::value>),
                            dim3(unsigned((waves + wpb - 1) / wpb)), dim3(sh.threads), sh.lds,
                            lc.stream, static_cast<const S *>(A), static_cast<S *>(B), gd);
@@ -127,20 +127,23 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     int64_t grid = bl.blocks > 0 ? std::min(bl.blocks, need) : need;
     grid = std::min<int64_t>(grid, 0x7fffffff);
     const StepPolicy sp = step_policy<LAT, S>(bl.bytes);
-    const int backwards = int(sp.reversed && bl.parity);
+    const int backwards = int(sp.keep > 0 && bl.parity);
+    const int64_t keep = keep_from(sp, bl.ntiles);
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         constexpr int EQ = decltype(E)::value, FO = decltype(O)::value;
         if (bl.walls)
             return with_wall_policy(sp.policy, [&](auto P) {
                 hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, true>),
                                    dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
-                                   bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards);
+                                   bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards,
+                                   keep);
                 return hipGetLastError();
             });
-        return with_policy(sp.policy, [&](auto P) {
+        return with_policy<LAT, S>(sp.policy, [&](auto P) {
             hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, false>),
                                dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
-                               bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards);
+                               bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards,
+                               keep);
             return hipGetLastError();
         });
     });
