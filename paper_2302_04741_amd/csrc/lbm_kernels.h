@@ -359,10 +359,17 @@ template <int LAT, class S> inline StepPolicy step_policy(int64_t T)
         return {Policy::STREAM_NT, std::min(0.57, 240e6 / t)};
     return {Policy::STREAM, std::min(0.55, 200e6 / t)};
 }
-// First of n work items, in the order of the sweep, whose stores are kept.
-inline int64_t keep_from(const StepPolicy &sp, int64_t n)
+// The order of one step's sweep over its work items (one argument of the kernels:
+// each costs the host a share of the launch).
+struct Sweep {
+    int64_t keep;   // first item, in the order of the sweep, whose stores are kept
+    int cur;        // buffer the step reads (a batch: flips each member's own)
+    int backwards;  // odd steps of a policy that keeps: last item first
+};
+inline Sweep sweep_of(const StepPolicy &sp, int64_t items, int cur)
 {
-    return n - int64_t(double(n) * sp.keep);
+    if (sp.keep <= 0) return {items, cur, 0};
+    return {items - int64_t(double(items) * sp.keep), cur, cur};
 }
 // Bytes of one population buffer in whole 128-byte lines.
 template <int LAT, class S> inline int64_t buffer_lines_bytes(const GridDims &gd)
@@ -524,15 +531,15 @@ template <int LAT, class S, int EQ, int FO, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     __attribute__((amdgpu_waves_per_eu(step_min_waves<S>(), 8)))
     step_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd, ForceDesc fd,
-                StepCoef co, uint32_t *ctr, int cur, int backwards, uint32_t keep)
+                StepCoef co, uint32_t *ctr, Sweep sw)
 {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(
-        swept_block(backwards) * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    const uint32_t step = step_number<S>(ctr, cur);
-    advance_step_number<S>(ctr, cur, step, wave == 0 && threadIdx.x == 0);
+        swept_block(sw.backwards) * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const uint32_t step = step_number<S>(ctr, sw.cur);
+    advance_step_number<S>(ctr, sw.cur, step, wave == 0 && threadIdx.x == 0);
     int x, y, z;
     if (!wave_cell(gd, wave, x, y, z)) return;
-    if (P != Policy::RESIDENT && blockIdx.x >= keep) {  // the sweep's last blocks (see Policy)
+    if (P != Policy::RESIDENT && blockIdx.x >= uint32_t(sw.keep)) {  // the sweep's last blocks (see Policy)
         keep_apart();
         step_cell<LAT, S, EQ, FO, P == Policy::RESIDENT ? P : Policy::KEEP>(A, B, gd, fd, co, x, y,
                                                                             z, step);
@@ -603,12 +610,12 @@ __global__ void __launch_bounds__(step_max_threads<S>())
 template <int LAT, class S, int EQ, int FO, Policy P, bool WALLS>
 __global__ void __launch_bounds__(256)
     multi_step_kernel(const int64_t *__restrict__ begin, const TileSim *__restrict__ sims,
-                      int nsims, int64_t ntiles, int parity, int backwards, int64_t keep)
+                      int nsims, int64_t ntiles, Sweep sw)
 {
     const int64_t nw = int64_t(gridDim.x) * (blockDim.x >> 6);
     int64_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     for (; w < ntiles; w += nw) {
-        const int64_t t = backwards ? ntiles - 1 - w : w;
+        const int64_t t = sw.backwards ? ntiles - 1 - w : w;
         // the simulation owning tile t: last k with begin[k] <= t (uniform)
         int lo = 0, hi = nsims - 1;
         while (lo < hi) {
@@ -625,7 +632,7 @@ __global__ void __launch_bounds__(256)
         const uint32_t zz = divu(sd.gd.by_ny, row);
         const int y = int(row - zz * uint32_t(sd.gd.ny)), z = int(zz);
         const int x = int(xc * 64u + (threadIdx.x & 63u));
-        const int c = sd.cur ^ parity;
+        const int c = sd.cur ^ sw.cur;
         const S *A = static_cast<const S *>(sd.pop[c]);
         S *B = static_cast<S *>(const_cast<void *>(sd.pop[c ^ 1]));
         // the member's step number; its first tile's wavefront advances it
@@ -642,7 +649,7 @@ __global__ void __launch_bounds__(256)
                 continue;
             }
         }
-        if (!WALLS && P != Policy::RESIDENT && w >= keep) {  // the sweep's last tiles
+        if (!WALLS && P != Policy::RESIDENT && w >= sw.keep) {  // the sweep's last tiles
             keep_apart();
             step_cell<LAT, S, EQ, FO, WALLS || P == Policy::RESIDENT ? P : Policy::KEEP>(
                 A, B, sd.gd, sd.fd, sd.co, x, y, z, step);

@@ -93,8 +93,7 @@ hipError_t launch_step_ls(int eq, int fo, const void *A, void *B, const GridDims
                                             decltype(P)::value>),
                                grid, dim3(sh.threads), sh.lds, lc.stream,
                                static_cast<const S *>(A), static_cast<S *>(B), gd, fd, co, lc.ctr,
-                               lc.cur, int(sp.keep > 0 && lc.cur),
-                               uint32_t(keep_from(sp, grid.x)));
+                               sweep_of(sp, grid.x, lc.cur));
             return hipGetLastError();
         });
     });
@@ -127,23 +126,20 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     int64_t grid = bl.blocks > 0 ? std::min(bl.blocks, need) : need;
     grid = std::min<int64_t>(grid, 0x7fffffff);
     const StepPolicy sp = step_policy<LAT, S>(bl.bytes);
-    const int backwards = int(sp.keep > 0 && bl.parity);
-    const int64_t keep = keep_from(sp, bl.ntiles);
+    const Sweep sw = sweep_of(sp, bl.ntiles, bl.parity);
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         constexpr int EQ = decltype(E)::value, FO = decltype(O)::value;
         if (bl.walls)
             return with_wall_policy(sp.policy, [&](auto P) {
                 hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, true>),
                                    dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
-                                   bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards,
-                                   keep);
+                                   bl.begin, bl.table, bl.nsims, bl.ntiles, sw);
                 return hipGetLastError();
             });
         return with_policy<LAT, S>(sp.policy, [&](auto P) {
             hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, false>),
                                dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
-                               bl.begin, bl.table, bl.nsims, bl.ntiles, bl.parity, backwards,
-                               keep);
+                               bl.begin, bl.table, bl.nsims, bl.ntiles, sw);
             return hipGetLastError();
         });
     });
