@@ -127,6 +127,12 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     grid = std::min<int64_t>(grid, 0x7fffffff);
     const StepPolicy sp = step_policy<LAT, S>(bl.bytes);
     const Sweep sw = sweep_of(sp, bl.ntiles, bl.parity);
+    // FP32 batches of 1 GiB a buffer and more: 8 wavefronts a CU, as in the step (us a
+    // step, 128 threads, limited against not: 64 grids of 64^2-1024^2, 3.1 GB, 1155 /
+    // 1168, 32 of them, 1.4 GB, 519 / 526, four D3Q39 128^3 476 / 503; 16 grids, 974 MB,
+    // 370 / 366: the last round of blocks counts there)
+    const bool limit = sizeof(S) == 4 && bl.blocks <= 0 && bl.bytes >= 1024 * MIB;
+    const unsigned lds = limit ? STEP_LDS_PER_CU * unsigned(bl.threads) / 512u : 0u;
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         constexpr int EQ = decltype(E)::value, FO = decltype(O)::value;
         if (bl.walls)
@@ -138,7 +144,7 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
             });
         return with_policy<LAT, S>(sp.policy, [&](auto P) {
             hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, false>),
-                               dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
+                               dim3(unsigned(grid)), dim3(unsigned(bl.threads)), lds, bl.stream,
                                bl.begin, bl.table, bl.nsims, bl.ntiles, sw);
             return hipGetLastError();
         });

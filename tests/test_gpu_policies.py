@@ -94,3 +94,39 @@ def test_f16_sizes_against_fp32(lattice, dims, what):
         s.close()
     for a, b, bar in zip(got["f16dev"], got["f32"], (2e-4, 2e-3, 2e-4)):
         assert float((a - b).abs().max()) <= bar * float(b.abs().max())
+
+
+# sides of the large member: the end of the sweep kept, the same with 8 wavefronts a CU
+# in FP32 (the batch of small members alone stays cached)
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16dev"])
+@pytest.mark.parametrize("lattice,small,sides", [("D2Q37", (200, 150, 1), (1000, 3000)),
+                                                 ("D3Q39", (40, 37, 33), (100, 200))])
+def test_batch_members_beside_a_large_one_bitwise(lattice, small, sides, storage):
+    """The policy follows the bytes of the whole batch and where a tile lies in the
+    sweep; a member's result depends on neither: bitwise what it is without the large
+    member, before it in the list or after."""
+    import torch
+
+    from paper_2302_04741_amd import sim, workloads
+
+    wls = [workloads.random_smooth(lattice, small, seed=3, tau_hat=0.7, force_kind=kind)
+           for kind in ("uniform", "axis")]
+
+    def run(members, picked):
+        sims = [sim.from_workload(w, storage=storage) for w in members]
+        b = sim.Batch(len(sims))
+        b.set(sims)
+        b.step(STEPS)
+        got = [sims[k].get_populations() for k in picked]
+        b.close()
+        for s in sims:
+            s.close()
+        return got
+
+    alone = run(wls, (0, 1))
+    for n in sides:
+        large = (workloads.thermal_shear_2d(n=n) if lattice == "D2Q37"
+                 else workloads.kolmogorov_3d(n=n))
+        for members, picked in (([wls[0], large, wls[1]], (0, 2)), ([large] + wls, (1, 2))):
+            for a, c in zip(alone, run(members, picked)):
+                assert torch.equal(a, c), (n, picked)
