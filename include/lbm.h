@@ -305,8 +305,9 @@ LBM_API lbm_status lbm_batch_create(int32_t max_sims, void *workspace, size_t wo
  * Destroying a member leaves the batch unusable until the next lbm_batch_set. */
 LBM_API lbm_status lbm_batch_set(lbm_batch *b, lbm_sim *const *sims, int32_t count);
 
-/* Advance every member by nsteps (>= 0) steps of eq. (lbm), one launch per
- * step, on the batch's stream.  The library does not order that stream with the members'
+/* Advance every member by nsteps (>= 0) steps of eq. (lbm) on the batch's stream:
+ * one launch per step, or, where the members' populations together exceed the
+ * memory-side cache, one per step and group of members.  The library does not order that stream with the members'
  * own streams: work queued on a member's stream must be complete (or ordered
  * with events) before, and later work on it must wait for the batch's stream
  * (the Python binding does both).  If a launch fails (LBM_EDEVICE), the steps

@@ -732,15 +732,25 @@ void fill_tile_sim(TileSim &t, const lbm_sim *s, int64_t first_tile)
     t.wd = s->wd;
 }
 
-// Write the tile table of `sims` (64-cell tiles) to begin[count + 1] and
-// tab[count] on `stream`; tiles = the length of the list, walls = some member
-// has plates, bytes = one population buffer of every member, in whole lines.
-hipError_t upload_table(lbm_sim *const *sims, int32_t count, int64_t *begin, TileSim *tab,
-                        hipStream_t stream, int64_t &tiles, bool &walls, int64_t &bytes)
+int64_t member_tiles(const lbm_sim *s)
 {
-    tiles = 0;
+    return (int64_t(s->p.nx) + 63) / 64 * s->p.ny * s->p.nz;
+}
+
+// One population buffer, in whole lines.
+int64_t member_bytes(const lbm_sim *s)
+{
+    const int64_t row = s->p.nx * int64_t(storage_bytes(s->p.storage));
+    return int64_t(s->Q) * s->p.ny * s->p.nz * ((row + 127) / 128 * 128);
+}
+
+// Write the tile table of `sims` (64-cell tiles) to begin[count + 1] and
+// tab[count] on `stream`; walls = some member has plates.
+hipError_t upload_table(lbm_sim *const *sims, int32_t count, int64_t *begin, TileSim *tab,
+                        hipStream_t stream, bool &walls)
+{
+    int64_t tiles = 0;
     walls = false;
-    bytes = 0;
     for (int32_t first = 0; first < count; first += TABLE_CHUNK) {
         TableChunk c;
         std::memset(&c, 0, sizeof c);
@@ -750,16 +760,113 @@ hipError_t upload_table(lbm_sim *const *sims, int32_t count, int64_t *begin, Til
             const lbm_sim *s = sims[first + k];
             fill_tile_sim(c.sims[k], s, tiles);
             c.begin[k] = tiles;
-            tiles += int64_t(c.sims[k].chunks_x) * s->p.ny * s->p.nz;
+            tiles += member_tiles(s);
             walls = walls || s->wd.on;
-            const int64_t row = s->p.nx * int64_t(storage_bytes(s->p.storage));
-            bytes += int64_t(s->Q) * s->p.ny * s->p.nz * ((row + 127) / 128 * 128);
         }
         c.last = first + c.n == count;
         c.end = tiles;
         hipLaunchKernelGGL(table_fill_kernel, dim3(1), dim3(64), 0, stream, c, begin, tab);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Members of a batch that advance together in one launch: a run of the list.
+struct Group {
+    int32_t first, end;
+    int64_t tile0, tiles, bytes;
+};
+
+// The members from `first` on that the memory-side cache holds together, about as many
+// bytes in each group of the batch; one that it does not hold is a group by itself,
+// with less than an eighth of the cache's worth before it, or left after it, taken in.
+Group next_group(lbm_sim *const *sims, int32_t count, int32_t first, int64_t tile0)
+{
+    int64_t left = 0;
+    for (int32_t k = first; k < count; ++k) left += member_bytes(sims[k]);
+    const int64_t groups = (left + STEP_CACHED_BYTES - 1) / STEP_CACHED_BYTES;
+    const int64_t share = left / std::max<int64_t>(1, groups);
+    Group g{first, first, tile0, 0, 0};
+    while (g.end < count) {
+        const int64_t more = member_bytes(sims[g.end]);
+        const bool few = g.bytes < STEP_CACHED_BYTES / 8 || left < STEP_CACHED_BYTES / 8;
+        if (!few && (g.bytes >= share || g.bytes + more > STEP_CACHED_BYTES)) break;
+        g.bytes += more;
+        left -= more;
+        g.tiles += member_tiles(sims[g.end++]);
+    }
+    return g;
+}
+
+// What step_groups enqueued: all steps of the members before `first`, `steps` of those
+// before `end`, none of the others.
+struct Enqueued {
+    int32_t first = 0, end = 0;
+    int64_t all = 0, steps = 0;
+    int64_t common(int32_t count) const
+    {
+        return first == count ? all : first == 0 && end == count ? steps : 0;
+    }
+    void advance(lbm_sim *const *sims, int32_t count) const
+    {
+        for (int32_t k = 0; k < count; ++k) {
+            const int64_t n = k < first ? all : k < end ? steps : 0;
+            sims[k]->cur ^= int(n & 1);
+            sims[k]->step += n;
+        }
+    }
+};
+
+// Enqueue nsteps steps of every member (`bl` but for the members, bl.parity that of the
+// first step).  Members do not read each other, so a batch larger than the cache runs
+// group by group, all the steps of one before the next: each reads its state from memory
+// once and from the cache after.  Us a step in calls of 25 steps, in groups against all
+// at once (bytes of one buffer): 64 grids of 64^2 to 1024^2 FP32, 3.1 GB, 1091 / 1155,
+// FP64 2091 / 2400; 16 of them FP32, 974 MB, 346 / 366; 12 of 512^2 FP32, 465 MB, 160 /
+// 169; four D3Q39 100^3 FP32, 592 MB, 256 / 311, F16 142 / 193; in calls of 4 steps it
+// gains nothing (1157 / 1155, F16 on 64 grids of 128^2 loses), of 8 half as much.  Below
+// twice the cached size the kept end of the sweep does as well (64 of 128^2 FP32,
+// 155 MB, 52.8 / 50.3), and D2Q37 in F16 is bound by its arithmetic in the cache (64 grids 634 /
+// 600).  A persistent grid, asked for with its number of blocks, walks the whole list.
+constexpr int64_t GROUP_MIN_STEPS = 8;
+hipError_t step_groups(lbm_sim *const *sims, int32_t count, BatchLaunch bl, int64_t nsteps,
+                       Enqueued &done)
+{
+    const lbm_sim *s0 = sims[0];
+    const int64_t *begin = bl.begin;
+    const TileSim *table = bl.table;
+    const int parity = bl.parity;
+    int64_t total = 0;
+    for (int32_t k = 0; k < count; ++k) total += member_bytes(sims[k]);
+    const bool arithmetic = s0->p.lattice == LBM_D2Q37 && storage_bytes(s0->p.storage) == 2;
+    const bool split = nsteps >= GROUP_MIN_STEPS && bl.blocks == 0 && !arithmetic &&
+                       total > 2 * STEP_CACHED_BYTES;
+    done = Enqueued{};
+    done.all = nsteps;
+    for (int64_t tile0 = 0; done.first < count;) {
+        Group g{0, count, 0, 0, 0};
+        if (split) {
+            g = next_group(sims, count, done.first, tile0);
+        } else {
+            for (int32_t k = 0; k < count; ++k) g.tiles += member_tiles(sims[k]);
+            g.bytes = total;
+        }
+        bl.begin = begin + g.first;
+        bl.table = table + g.first;
+        bl.nsims = g.end - g.first;
+        bl.tile0 = g.tile0;
+        bl.ntiles = g.tiles;
+        bl.bytes = g.bytes;
+        done.end = g.end;
+        for (done.steps = 0; done.steps < nsteps; ++done.steps) {
+            bl.parity = parity ^ int(done.steps & 1);
+            hipError_t e = launch_multi_step(s0->p.lattice, s0->p.storage, s0->eq,
+                                             s0->p.force_order, bl);
+            if (e != hipSuccess) return e;
+        }
+        done.first = g.end;
+        tile0 += g.tiles;
     }
     return hipSuccess;
 }
@@ -776,11 +883,9 @@ struct lbm_batch {
     std::vector<int64_t> gen_at_set;   // members' launch-argument generations then
     int64_t generation;                // bumped whenever the table or launch shape changes
     int64_t steps_done;                // batch steps since the table was built
-    int64_t ntiles;
     int threads;     // threads per block (tiles of 64 cells, one per wavefront)
     int64_t blocks;  // 0: one block per tile
     bool walls;           // some member has plates
-    int64_t bytes;        // one population buffer of every member together, whole lines
 };
 
 struct lbm_graph {
@@ -824,20 +929,20 @@ hipError_t batch_wall_densities(lbm_batch *b)
     return hipSuccess;
 }
 
-// Enqueues nsteps batch steps; done is the number enqueued (all of them unless
+// Enqueues nsteps batch steps; done says what was enqueued (all of them unless
 // a launch failed).
-lbm_status batch_launch(lbm_batch *b, int64_t nsteps, int64_t &done)
+lbm_status batch_launch(lbm_batch *b, int64_t nsteps, Enqueued &done)
 {
-    const lbm_sim *s0 = b->sims[0];
-    for (done = 0; done < nsteps; ++done) {
-        const int parity = int((b->steps_done + done) & 1);
-        const BatchLaunch bl{b->begin,  b->table,   int(b->sims.size()), b->ntiles, parity,
-                             b->threads, b->blocks, b->stream,           b->walls,  b->bytes};
-        hipError_t e = launch_multi_step(s0->p.lattice, s0->p.storage, s0->eq, s0->p.force_order,
-                                         bl);
-        if (e != hipSuccess) return dev_fail(e, "multi-grid step launch");
-    }
-    return LBM_OK;
+    BatchLaunch bl{};
+    bl.begin = b->begin;
+    bl.table = b->table;
+    bl.parity = int(b->steps_done & 1);
+    bl.threads = b->threads;
+    bl.blocks = b->blocks;
+    bl.stream = b->stream;
+    bl.walls = b->walls;
+    hipError_t e = step_groups(b->sims.data(), int32_t(b->sims.size()), bl, nsteps, done);
+    return e == hipSuccess ? LBM_OK : dev_fail(e, "multi-grid step launch");
 }
 
 // Set the members and write their tile table into the batch workspace on the
@@ -846,10 +951,8 @@ lbm_status batch_build(lbm_batch *b, lbm_sim *const *sims, int32_t count)
 {
     lbm_status st = check_members(sims, count);
     if (st != LBM_OK) return st;
-    int64_t tiles = 0;
     bool walls = false;
-    int64_t bytes = 0;
-    hipError_t e = upload_table(sims, count, b->begin, b->table, b->stream, tiles, walls, bytes);
+    hipError_t e = upload_table(sims, count, b->begin, b->table, b->stream, walls);
     if (e != hipSuccess) return dev_fail(e, "tile table fill launch");
     b->sims.assign(sims, sims + count);
     b->step_at_set.clear();
@@ -860,9 +963,7 @@ lbm_status batch_build(lbm_batch *b, lbm_sim *const *sims, int32_t count)
     }
     b->steps_done = 0;
     b->generation++;
-    b->ntiles = tiles;
     b->walls = walls;
-    b->bytes = bytes;
     return LBM_OK;
 }
 
@@ -905,12 +1006,10 @@ lbm_status lbm_batch_create(int32_t max_sims, void *workspace, size_t workspace_
     b->begin = reinterpret_cast<int64_t *>(b->ws);
     b->table = reinterpret_cast<TileSim *>(b->ws + batch_begin_bytes(max_sims));
     b->steps_done = 0;
-    b->ntiles = 0;
     b->generation = 0;
     b->threads = BATCH_DEFAULT_THREADS;
     b->blocks = 0;
     b->walls = false;
-    b->bytes = 0;
     *out = b;
     return ok();
 }
@@ -936,9 +1035,12 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps)
     TraceRange range("lbm_batch_step");
     hipError_t e = batch_wall_densities(b);
     if (e != hipSuccess) return dev_fail(e, "wall density kernel launch");
-    int64_t done = 0;
+    Enqueued done;
     st = batch_launch(b, nsteps, done);
-    batch_advance(b, done);  // the steps enqueued before a failed launch still run
+    // the steps enqueued before a failed launch still run; members that are not at the
+    // same step any more need a new table
+    done.advance(b->sims.data(), int32_t(b->sims.size()));
+    b->steps_done += done.common(int32_t(b->sims.size()));
     if (st != LBM_OK) {
         for (lbm_sim *s : b->sims) s->wall_fresh = false;
         return st;
@@ -1031,26 +1133,20 @@ lbm_status lbm_batch_step_noalloc(lbm_sim *const *sims, int32_t count, int64_t n
     }
     int64_t *begin = reinterpret_cast<int64_t *>(base);
     TileSim *table = reinterpret_cast<TileSim *>(base + NOALLOC_BEGIN_BYTES);
-    int64_t tiles = 0;
-    bool walls = false;
-    int64_t bytes = 0;
-    e = upload_table(sims, count, begin, table, stream, tiles, walls, bytes);
+    BatchLaunch bl{};
+    bl.begin = begin;
+    bl.table = table;
+    bl.threads = BATCH_DEFAULT_THREADS;
+    bl.stream = stream;
+    e = upload_table(sims, count, begin, table, stream, bl.walls);
     if (e != hipSuccess) return dev_fail(e, "tile table fill launch");
-    const lbm_sim *s0 = sims[0];
-    int64_t done = 0;
-    for (; done < nsteps; ++done) {
-        const BatchLaunch bl{begin,  table, int(count), tiles, int(done & 1), BATCH_DEFAULT_THREADS,
-                             0,      stream, walls, bytes};
-        e = launch_multi_step(s0->p.lattice, s0->p.storage, s0->eq, s0->p.force_order, bl);
-        if (e != hipSuccess) break;
+    Enqueued done;
+    e = step_groups(sims, count, bl, nsteps, done);
+    done.advance(sims, count);
+    if (e != hipSuccess) {
+        for (int32_t k = 0; k < count; ++k) sims[k]->wall_fresh = false;
+        return dev_fail(e, "multi-grid step launch");
     }
-    // the steps enqueued before a failed launch still run
-    for (int32_t k = 0; k < count; ++k) {
-        sims[k]->cur ^= int(done & 1);
-        sims[k]->step += done;
-        if (e != hipSuccess) sims[k]->wall_fresh = false;
-    }
-    if (e != hipSuccess) return dev_fail(e, "multi-grid step launch");
     return ok();
 }
 
@@ -1098,7 +1194,7 @@ lbm_status lbm_graph_create(lbm_sim *s, lbm_batch *b, int64_t nsteps, lbm_graph 
         hipError_t el = launch_steps(s, cur, nsteps, done);
         if (el != hipSuccess) st = dev_fail(el, "step launch during capture");
     } else {
-        int64_t done = 0;
+        Enqueued done;
         st = batch_launch(b, nsteps, done);
     }
     hipGraph_t graph = nullptr;

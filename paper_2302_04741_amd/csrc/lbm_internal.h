@@ -795,18 +795,21 @@ hipError_t launch_convert(int storage, const double *src, void *dst, int64_t n,
 // rows of all Q planes; `dense` aligned to the stored type (rows.hip)
 hipError_t launch_copy_rows(int storage, void *padded, void *dense, const GridDims &gd, int Q,
                             bool exporting, hipStream_t stream);
+constexpr int64_t MIB = int64_t(1) << 20;
+constexpr int64_t STEP_CACHED_BYTES = 128 * MIB;  // two such buffers fit the memory-side cache
 // One launch of the multi-grid step: tile list, its members, launch shape.
 struct BatchLaunch {
     const int64_t *begin;   // device: first tile of member k (k < nsims), ascending
     const TileSim *table;   // device: the members
     int nsims;
-    int64_t ntiles;         // tiles of all members
+    int64_t tile0;          // the first member's first tile
+    int64_t ntiles;         // tiles of these members
     int parity;             // batch steps since the table was built, mod 2
     int threads;            // threads per block (64, 128 or 256): 1, 2 or 4 tiles
     int64_t blocks;         // 0: one block per tile; > 0: persistent walk
     hipStream_t stream;
-    bool walls;             // some member has plates (the kernel variant that handles them)
-    int64_t bytes;          // one population buffer of every member together, whole lines
+    bool walls;             // some member of the batch has plates (the kernel variant)
+    int64_t bytes;          // one population buffer of these members together, whole lines
 };
 hipError_t launch_multi_step(int lat, int storage, int eq, int fo, const BatchLaunch &bl);
 // plates: emission tables, the row sums of a state no step produced, and the

@@ -293,8 +293,6 @@ struct StepShape {
 // and F16, with half the bytes a wavefront, loses (256^3 700 / 496); F16 of 1 GiB a
 // buffer and more takes 512 threads unlimited (256^3 476 / 490, D2Q37 4096^2 441 /
 // 458; below it is within 2% either way).
-constexpr int64_t MIB = int64_t(1) << 20;
-constexpr int64_t STEP_CACHED_BYTES = 128 * MIB;  // two such buffers fit the memory-side cache
 constexpr int64_t STEP_LARGE_BYTES = 400 * MIB;
 constexpr unsigned STEP_LDS_PER_CU = 160u << 10;
 
@@ -362,14 +360,15 @@ template <int LAT, class S> inline StepPolicy step_policy(int64_t T)
 // The order of one step's sweep over its work items (one argument of the kernels:
 // each costs the host a share of the launch).
 struct Sweep {
+    int64_t first;  // a batch: first tile of the launch
     int64_t keep;   // first item, in the order of the sweep, whose stores are kept
     int cur;        // buffer the step reads (a batch: flips each member's own)
     int backwards;  // odd steps of a policy that keeps: last item first
 };
-inline Sweep sweep_of(const StepPolicy &sp, int64_t items, int cur)
+inline Sweep sweep_of(const StepPolicy &sp, int64_t items, int cur, int64_t first = 0)
 {
-    if (sp.keep <= 0) return {items, cur, 0};
-    return {items - int64_t(double(items) * sp.keep), cur, cur};
+    if (sp.keep <= 0) return {first, items, cur, 0};
+    return {first, items - int64_t(double(items) * sp.keep), cur, cur};
 }
 // Bytes of one population buffer in whole 128-byte lines.
 template <int LAT, class S> inline int64_t buffer_lines_bytes(const GridDims &gd)
@@ -615,7 +614,7 @@ __global__ void __launch_bounds__(256)
     const int64_t nw = int64_t(gridDim.x) * (blockDim.x >> 6);
     int64_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     for (; w < ntiles; w += nw) {
-        const int64_t t = sw.backwards ? ntiles - 1 - w : w;
+        const int64_t t = sw.first + (sw.backwards ? ntiles - 1 - w : w);
         // the simulation owning tile t: last k with begin[k] <= t (uniform)
         int lo = 0, hi = nsims - 1;
         while (lo < hi) {

@@ -126,7 +126,7 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     int64_t grid = bl.blocks > 0 ? std::min(bl.blocks, need) : need;
     grid = std::min<int64_t>(grid, 0x7fffffff);
     const StepPolicy sp = step_policy<LAT, S>(bl.bytes);
-    const Sweep sw = sweep_of(sp, bl.ntiles, bl.parity);
+    const Sweep sw = sweep_of(sp, bl.ntiles, bl.parity, bl.tile0);
     // FP32 batches of 1 GiB a buffer and more: 8 wavefronts a CU, as in the step (us a
     // step, 128 threads, limited against not: 64 grids of 64^2-1024^2, 3.1 GB, 1155 /
     // 1168, 32 of them, 1.4 GB, 519 / 526, four D3Q39 128^3 476 / 503; 16 grids, 974 MB,

@@ -130,3 +130,53 @@ def test_batch_members_beside_a_large_one_bitwise(lattice, small, sides, storage
         for members, picked in (([wls[0], large, wls[1]], (0, 2)), ([large] + wls, (1, 2))):
             for a, c in zip(alone, run(members, picked)):
                 assert torch.equal(a, c), (n, picked)
+
+
+# members the memory-side cache does not hold, holds one by one, and small ones between
+@pytest.mark.parametrize("lattice,storage,sides", [
+    ("D2Q37", "f32", (1200, 40, 33, 700, 512, 600, 65)),
+    ("D2Q37", "f64", (50, 700, 64, 900, 512, 33)),
+    ("D3Q39", "f32", (24, 100, 90, 17, 70, 64)),
+    ("D3Q39", "f16dev", (100, 24, 100, 100, 96, 17)),
+])
+def test_batch_in_groups_equals_step_by_step_bitwise(lattice, storage, sides):
+    """Calls of many steps advance a large batch group by group, calls of one step all
+    members together: the same states, whoever makes the call."""
+    import torch
+
+    from paper_2302_04741_amd import sim, workloads
+
+    steps = 9
+
+    def members():
+        return [sim.from_workload(workloads.thermal_shear_2d(n=n) if lattice == "D2Q37"
+                                  else workloads.kolmogorov_3d(n=n), storage=storage)
+                for n in sides]
+
+    def finish(sims):
+        got = [s.get_populations() for s in sims]
+        assert all(s.step_count == steps for s in sims)
+        for s in sims:
+            s.close()
+        return got
+
+    sims = members()
+    b = sim.Batch(len(sims))
+    b.set(sims)
+    for _ in range(steps):
+        b.step(1)
+    b.close()
+    want = finish(sims)
+
+    sims = members()
+    b = sim.Batch(len(sims))
+    b.set(sims)
+    b.step(steps)
+    b.close()
+    for a, c in zip(want, finish(sims)):
+        assert torch.equal(a, c)
+
+    sims = members()
+    sim.batch_step_noalloc(sims, steps)
+    for a, c in zip(want, finish(sims)):
+        assert torch.equal(a, c)
