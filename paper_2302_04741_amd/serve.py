@@ -5,7 +5,8 @@ steps) arrive over time.  The server admits a request as soon as a slot and
 enough of its HBM budget are free, keeps every admitted simulation's
 populations resident in its own workspace, and advances all admitted
 simulations together: each chunk of steps is one launch per step of the
-multi-grid kernel over every member (the batch is re-formed whenever
+multi-grid kernel over every member, or over each group of members that the
+memory-side cache holds together (the batch is re-formed whenever
 membership changes).  Requests that arrive while others run join at the next
 chunk boundary; finished requests release their slot and memory as soon as
 their last chunk has run.  A member that diverges (non-finite totals) fails
