@@ -70,9 +70,9 @@ typedef enum { LBM_D2Q37 = 0, LBM_D3Q39 = 1 } lbm_lattice;
  * The step stores LBM_F16DEV values with stochastic rounding (up or down with
  * probabilities that make the rounding error zero-mean; lbm_round_f16_stochastic
  * applies the same rounding to plain arrays), its random bits drawn from a
- * hash of (cell, step number) walked once per population: deterministic, and
- * independent of launch shape, batching and the other members; the initial
- * state rounds to nearest. */
+ * sequence that a hash of (cell, step number) starts, word i for the population
+ * of plane i: deterministic, and independent of launch shape, batching and the
+ * other members; the initial state rounds to nearest. */
 typedef enum { LBM_F64 = 0, LBM_F32 = 1, LBM_F16DEV = 2 } lbm_storage;
 
 /* Truncation of the force expansion eq. (F).  The paper's N = 0, 1, 2 are

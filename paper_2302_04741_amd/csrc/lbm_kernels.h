@@ -35,12 +35,12 @@ template <> struct ArithOf<__half> { using type = float; };
 // Random bits of the F16 stochastic rounding.  One 32-bit key per (cell,
 // step): the cell index and the step number combined linearly, then the
 // 32-bit finalizer of MurmurHash3 (Appleby) to spread every input bit over
-// the word.  The cell's stores then walk a 32-bit linear congruential
-// sequence from that key (Knuth's multiplier 6364136223846793005 reduced to
-// its low word, odd increment), each store taking the current word whole as
-// the seed of its conversion (half_sr reads its top 13 bits, the sequence's
-// best ones).  Nothing depends on the launch shape, the batch or the other
-// members.
+// the word.  From that key runs a 32-bit linear congruential sequence (Knuth's
+// multiplier 6364136223846793005 reduced to its low word, odd increment), and
+// the population of plane i takes word i of it, whole, as the seed of its
+// conversion (half_sr reads its top 13 bits, the sequence's best ones).  Nothing
+// depends on the launch shape, the batch, the other members or the order in
+// which the planes are stored.
 __device__ __forceinline__ uint32_t sr_key(uint32_t cell, uint32_t step)
 {
     uint32_t h = cell * 0x9E3779B1u + step * 0x85EBCA77u;
@@ -51,13 +51,36 @@ __device__ __forceinline__ uint32_t sr_key(uint32_t cell, uint32_t step)
     h ^= h >> 16;
     return h;
 }
-struct SrStream {
-    uint32_t x;
-    __device__ __forceinline__ uint32_t next()
+// The sequence d words on, for d in [-N, N]: x -> mul[d + N] x + add[d + N]  (mod 2^32).
+struct SrJump {
+    static constexpr int N = 40;
+    uint32_t mul[2 * N + 1], add[2 * N + 1];
+    constexpr SrJump() : mul{}, add{}
     {
-        const uint32_t r = x;
-        x = x * 0x4C957F2Du + 0x2545F491u;
-        return r;
+        constexpr uint32_t m = 0x4C957F2Du, a = 0x2545F491u;
+        uint32_t inv = m;  // 1 / m mod 2^32: Newton's iteration doubles the correct bits
+        for (int k = 0; k < 5; ++k) inv *= 2u - m * inv;
+        mul[N] = 1u;
+        for (int d = 1; d <= N; ++d) {
+            mul[N + d] = mul[N + d - 1] * m;
+            add[N + d] = add[N + d - 1] * m + a;
+            mul[N - d] = mul[N - d + 1] * inv;
+            add[N - d] = (add[N - d + 1] - a) * inv;
+        }
+    }
+};
+static constexpr SrJump SR_JUMP{};
+struct SrStream {
+    uint32_t x;  // word `at`
+    int at;
+    // word i (a compile-time index: planes stored in sequence cost one step each,
+    // the four gaps in the order of the orbits a step with other constants)
+    __device__ __forceinline__ uint32_t word(int i)
+    {
+        const int d = i - at + SrJump::N;
+        x = x * SR_JUMP.mul[d] + SR_JUMP.add[d];
+        at = i;
+        return x;
     }
 };
 
@@ -119,11 +142,11 @@ template <class L> struct Codec<L, __half> {
     {
         return T(__half2float(v));
     }
-    // stochastic rounding (half_sr), seeded by the next word of the cell's stream
+    // stochastic rounding (half_sr), seeded by the plane's word of the cell's stream
     template <int I, class T> __device__ static __forceinline__ __half store_scaled(T h,
                                                                                    SrStream &rng)
     {
-        return half_sr(float(h), rng.next());
+        return half_sr(float(h), rng.word(I));
     }
 };
 
@@ -405,7 +428,7 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
     // storage is reduced-precision); the sums and the pair terms take the
     // scale through their constants, so no value is rescaled on the way.
     using C = Codec<L, S>;
-    SrStream rng{C::STOCHASTIC ? sr_key(uint32_t(cell), step) : 0u};
+    SrStream rng{C::STOCHASTIC ? sr_key(uint32_t(cell), step) : 0u, 0};
     T h[L::Q];
     gather<L, S, T, WALLS, CacheBits<P>::load>(A, gd, x, y, z, h, wd, co.rho0);
     T g[3];
