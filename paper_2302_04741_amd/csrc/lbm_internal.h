@@ -544,10 +544,10 @@ __device__ __forceinline__ void finish_moments(const RawSums<T> &s, const T g[3]
 //     odd part  w rho xg                                       (order 1, 2)
 //               w rho [xg (1 + (xu^2 - u2 + t(X2 - D - 2))/2) - gu xu]   (order >= 3)
 //               - (w/2) [xg (xi.sigma.xi) - 2 xi.sigma.g]     (order 4)
-// With NO_BASE the even part omits alpha * w * rho (the leading term of f0);
-// w * base is added to it (callers pass the exactly rounded increment of that
-// leading term).  With a scale SC every w is w * SC::scale<i>() (a power of
-// two): even and odd come out multiplied by it exactly.
+// The even part omits alpha * w * rho (the leading term of f0) and has w * base added
+// (callers pass the rounded increment of that leading term, or add it themselves).
+// With a scale SC every w is w * SC::scale<i>() (a power of two): even and odd come
+// out multiplied by it exactly.
 // The callback receives (i_plus, i_minus, even, odd) for each pair and
 // (0, -1, even, 0) for the rest velocity; the indices are passed as
 // std::integral_constant so that callers index register arrays statically.
@@ -557,15 +557,24 @@ __device__ __forceinline__ void finish_moments(const RawSums<T> &s, const T g[3]
 // they are computed once a cell and each orbit of sign flips needs its sign
 // parts only: with |c| = (k_x, k_y, k_z)
 //   even/w = E + sum_{a<b} sign_a sign_b E_ab,  odd/w = sum_a sign_a O_a (+ sign_xyz O_xyz),
-//   E    = C + sum_a k_a^2 (K_a + k_a^2 Q_a) + k_x^2 k_y^2 Q_xy      (Q: N = 4, D = 2)
+//   E    = C + T (X2 - D) + sum_a k_a^2 (K_a + k_a^2 Q_a) + k_x^2 k_y^2 Q_xy
+//                                                     (T = alpha rho t/2; Q: N = 4, D = 2)
 //   E_ab = k_a k_b (K_ab + k_a^2 Q_aab + k_b^2 Q_abb)
 //   O_a  = k_a (G_a + sum_b k_b^2 H_ab),   O_xyz = k_x k_y k_z H_xyz
 // and the 2, 4 or 8 velocities of the orbit are the butterflies of those parts.
 // Against xi.u, xi.g and xi.sigma.xi dotted out for each pair this halves the
 // step's vector instructions (counts and times at step_cell).
+//
+// A rounding error of a coefficient that all populations share goes into the conserved
+// sums whole, as sum w = 1.  So the large isotropic term T (X2 - D) is added shell by
+// shell, and C is what makes the even parts sum to base for the K and Q as they were
+// rounded (sum w c_a^2 = 1/r^2, sum w c_a^4 = 3/r^4, sum w c_a^2 c_b^2 = 1/r^4).  Rms
+// change of the mass in one FP32 collision, speeds to 0.05: D2Q37 1.4e-9, D3Q39
+// 1.7e-9; with the closed form of C and all of it in one constant 2.9e-9 and 3.6e-9,
+// with xi.u dotted out for each pair 2.5e-9 and 2.6e-9; speeds to 1.5 along x 6.6e-8
+// and 7.5e-8 against 9.3e-8 and 1.0e-7 pair by pair.
 // ---------------------------------------------------------------------------
-template <class L, class T, int EQ, int FO, bool NO_BASE = false, class SC = UnitScale,
-          class CB>
+template <class L, class T, int EQ, int FO, class SC = UnitScale, class CB>
 __device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T beta, T base,
                                             CB &&cb)
 {
@@ -585,50 +594,20 @@ __device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T b
     const T arho = alpha * cs.rho, brho = beta * cs.rho, brgu = brho * gu;
     const T half_t = T(0.5) * t;
 
-    // polynomials in X2 of the even part's constant E0 + E1 X2 + E2 X2^2, of its
-    // xu^2 factor D0 + D1 X2, and of the odd part's xu factor G0 + G1 X2
-    T E0 = T(-0.5) * fma_t(T(D), t, u2), E1 = half_t, E2 = T(0);
-    T D0 = T(0.5), D1 = T(0);
-    if constexpr (!NO_BASE) E0 += T(1);
+    // polynomials in X2 of the even part's xu^2 factor D0 + D1 X2 and of the odd
+    // part's xu factor G0 + G1 X2
+    T D0 = T(0.5), D1 = T(0), tt = T(0), tu = T(0);
     if constexpr (EQ == 4) {
-        // [3 u2^2 + 6 t u2 (D + 2 - X2) + 3 t^2 (X2^2 - 2 (D + 2) X2 + D (D + 2))] / 24
-        const T tt = t * t;
-        const T tu = t * u2;
-        E0 += fma_t(T(0.125) * u2, u2, fma_t(T(0.25 * (D + 2)), tu, T(0.125 * D * (D + 2)) * tt));
-        E1 -= T(0.25) * fma_t(T(D + 2), tt, tu);
-        E2 = T(0.125) * tt;
+        tt = t * t;
+        tu = t * u2;
         // (t (X2 - D - 4) - u2) / 4
         D0 -= T(0.25) * fma_t(T(D + 4), t, u2);
         D1 = T(0.25) * t;
     }
     const T G0 = T(1) - fma_t(half_t, T(D + 2), T(0.5) * u2), G1 = half_t;
 
-    // even coefficients
-    T C = fma_t(arho, E0, base);
-    if constexpr (FO >= 2) C -= brgu;
-    T K[3], Kab[3][3], Q[3] = {T(0), T(0), T(0)}, Qxy = T(0), Qab[2] = {T(0), T(0)};
-    {
-        const T e1 = arho * E1 * r2;
-        const T m = arho * D0;
-        T V[3];  // half the quadratic form's vector: K_ab = U_a V_b + U_b V_a
-        for (int a = 0; a < D; ++a) V[a] = FO >= 2 ? fma_t(m, U[a], brho * G[a]) : m * U[a];
-        for (int a = 0; a < D; ++a) {
-            K[a] = fma_t(U[a], V[a], e1);
-            for (int b = a + 1; b < D; ++b) Kab[a][b] = fma_t(U[a], V[b], U[b] * V[a]);
-        }
-        if constexpr (EQ == 4) {
-            const T e2 = arho * E2 * T(L::R2 * L::R2);
-            const T d1 = arho * D1 * r2;
-            const T a24 = arho * T(1.0 / 24.0);
-            const T xx = U[0] * U[0], yy = U[1] * U[1], xy = U[0] * U[1];
-            Q[0] = fma_t(xx, fma_t(a24, xx, d1), e2);
-            Q[1] = fma_t(yy, fma_t(a24, yy, d1), e2);
-            Qxy = fma_t(d1, xx + yy, fma_t(T(6) * a24 * xx, yy, T(2) * e2));
-            Qab[0] = xy * fma_t(T(4) * a24, xx, T(2) * d1);
-            Qab[1] = xy * fma_t(T(4) * a24, yy, T(2) * d1);
-        }
-    }
-    // odd coefficients
+    // odd coefficients (first: the other way round the FP64 step on D3Q39 takes 8
+    // registers more a lane, and its batch kernel drops to two wavefronts a SIMD)
     constexpr bool CUBIC = EQ >= 3 || FO >= 3;
     T O[3], H[3][3], Hxyz = T(0);
     {
@@ -684,9 +663,41 @@ __device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T b
         }
     }
 
+    // even coefficients
+    const T iso = arho * half_t;
+    T K[3], Kab[3][3], Q[3] = {T(0), T(0), T(0)}, Qxy = T(0), Qab[2] = {T(0), T(0)}, C;
+    {
+        const T m = arho * D0;
+        T V[3];  // half the quadratic form's vector: K_ab = U_a V_b + U_b V_a
+        for (int a = 0; a < D; ++a) V[a] = FO >= 2 ? fma_t(m, U[a], brho * G[a]) : m * U[a];
+        // the fourth order's X2 and X2^2: -t (u2 + (D + 2) t) / 4 and t^2 / 8
+        const T e1 = arho * T(-0.25 * L::R2) * fma_t(T(D + 2), tt, tu);
+        for (int a = 0; a < D; ++a) {
+            K[a] = EQ == 4 ? fma_t(U[a], V[a], e1) : U[a] * V[a];
+            for (int b = a + 1; b < D; ++b) Kab[a][b] = fma_t(U[a], V[b], U[b] * V[a]);
+        }
+        T sum = K[0];
+        for (int a = 1; a < D; ++a) sum += K[a];
+        if constexpr (EQ == 4) {
+            const T e2 = arho * tt * T(0.125 * L::R2 * L::R2);
+            const T d1 = arho * D1 * r2;
+            const T a24 = arho * T(1.0 / 24.0);
+            const T xx = U[0] * U[0], yy = U[1] * U[1], xy = U[0] * U[1];
+            Q[0] = fma_t(xx, fma_t(a24, xx, d1), e2);
+            Q[1] = fma_t(yy, fma_t(a24, yy, d1), e2);
+            Qxy = fma_t(d1, xx + yy, fma_t(T(6) * a24 * xx, yy, T(2) * e2));
+            Qab[0] = xy * fma_t(T(4) * a24, xx, T(2) * d1);
+            Qab[1] = xy * fma_t(T(4) * a24, yy, T(2) * d1);
+            sum = fma_t(T(1.0 / L::R2), fma_t(T(3), Q[0] + Q[1], Qxy), sum);
+        }
+        C = fma_t(T(-1.0 / L::R2), sum, base);
+    }
+    // C + T (X2 - D) of a shell
+    auto isotropic = [&](double X2) { return fma_t(T(X2 - D), iso, C); };
     // rest velocity
     constexpr double w0 = L::wshell(L::shell(0)) * SC::template scale<0>();
-    cb(std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{}, T(w0) * C, T(0));
+    cb(std::integral_constant<int, 0>{}, std::integral_constant<int, -1>{},
+       T(w0) * isotropic(0.0), T(0));
 
     // orbits on the axes first: they need no mixed coefficient, so the populations
     // they take are gone before those are formed (two FP64 registers a lane)
@@ -730,7 +741,7 @@ __device__ __forceinline__ void combo_pairs(const CellState<T> &cs, T alpha, T b
         using A0 = std::integral_constant<int, a0>;
         using A1 = std::integral_constant<int, a1>;
         using A2 = std::integral_constant<int, a2>;
-        T e = even1(A0{}, C);
+        T e = even1(A0{}, isotropic(L::R2 * c2<L>(i)));
         if constexpr (o.n == 1) {
             emit(std::integral_constant<int, 0>{}, T(w) * e, odd1(A0{}));
         } else if constexpr (o.n == 2) {

@@ -407,8 +407,8 @@ template <int LAT, class S> inline int64_t buffer_lines_bytes(const GridDims &gd
 //
 // Bound by memory on large grids and by the length of its instruction stream on
 // small ones (one wavefront a SIMD or fewer: each instruction is latency).  The
-// stream is 925 instructions for D2Q37 FP32 (523 vector, 324 scalar) and 1051 for
-// D3Q39 FP32 (579, 388); with the pair-by-pair evaluation, looping wraps and a
+// stream is 938 instructions for D2Q37 FP32 (535 vector, 325 scalar) and 1058 for
+// D3Q39 FP32 (586, 388); with the pair-by-pair evaluation, looping wraps and a
 // resource made for each access it was 1860 and 2211.  Step of D2Q37 64^2 FP64:
 // 5.7 -> 4.7 us, of the plated 3 x 150 channel 15.3 -> 12.2 us, of D2Q37 256^2 FP32
 // 8.4 -> 7.9 us; at 1024^2 and above the memory time hid most of it already.
@@ -440,9 +440,9 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
 
     // h* = h + om (f0 - f) + cf F with f0 - f = w drho + (f0 - w rho) - h, so
     // h* = (1 - om) h + [om w drho + om (f0 - w rho) + cf F]; the bracket is what
-    // combo_pairs returns with NO_BASE and base = om drho (even +- odd part), each
-    // population one fma of it (1 - om is exact for om = 1/tau^ in [1/2, 2]).
-    // Every term is a small deviation, so the rounding stays at the size of h.
+    // combo_pairs returns with base = om drho (even +- odd part), each population one
+    // fma of it (1 - om is exact for om = 1/tau^ in [1/2, 2]).  Every term is a small
+    // deviation, so the rounding stays at the size of h.
     const T om = cs.om;
     const T omc = T(1) - om;
     const uint32_t xo = uint32_t(x) * uint32_t(sizeof(S));
@@ -460,8 +460,7 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
                 ps[cy + 3] += Codec<L, S>::template load<i, double>(stored);
         }
     };
-    combo_pairs<L, T, EQ, FO, true, C>(cs, om, cs.cf, om * cs.drho,
-                                       [&](auto IP, auto IM, T ev, T od) {
+    combo_pairs<L, T, EQ, FO, C>(cs, om, cs.cf, om * cs.drho, [&](auto IP, auto IM, T ev, T od) {
         constexpr int ip = decltype(IP)::value;
         constexpr int im = decltype(IM)::value;
         auto relaxed = [&](T hi, T sign_od) { return fma_t(omc, hi, ev + sign_od); };
@@ -710,8 +709,8 @@ __device__ __forceinline__ void scatter_initial(const CellState<T> &cs, S *__res
     PlaneWalk planes(A, uint32_t(gd.P * int64_t(sizeof(S))));
     constexpr int FOI = FO == 4 ? 3 : FO;  // sigma = 0 at the start
     // h = w (rho - rho0) + (f0 - w rho) - F/2
-    combo_pairs<L, T, EQ, FOI, true>(cs, T(1), T(-0.5), cs.drho,
-                                     [&](auto IP, auto IM, T ev, T od) {
+    combo_pairs<L, T, EQ, FOI>(cs, T(1), T(-0.5), T(0), [&](auto IP, auto IM, T ev, T od) {
+        constexpr double w = L::wshell(L::shell(decltype(IP)::value));
         auto put = [&](auto II, T v) {
             constexpr int i = decltype(II)::value;
             constexpr int cx = L::c(i, 0), cy = L::c(i, 1), cz = L::c(i, 2);
@@ -727,8 +726,8 @@ __device__ __forceinline__ void scatter_initial(const CellState<T> &cs, S *__res
             }
             BufIO<S>::template store<BUF_DEFAULT>(sv, plane, at.xs[cx + 3], at.row(cy, cz));
         };
-        put(IP, ev + od);
-        if constexpr (decltype(IM)::value >= 0) put(IM, ev - od);
+        put(IP, fma_t(T(w), cs.drho, ev + od));
+        if constexpr (decltype(IM)::value >= 0) put(IM, fma_t(T(w), cs.drho, ev - od));
     });
 }
 
@@ -868,18 +867,19 @@ __global__ void __launch_bounds__(256)
         }
         for (int a = 0; a < L::D; ++a) qa[a] += d * cc * cv[a];
     };
-    combo_pairs<L, T, EQ, FO, true>(cs, -cf, T(0.5) * cf, -cf * cs.drho,
-                                    [&](auto IP, auto IM, T ev, T od) {
+    // h - w drho first: both are of the size of drho (with rho0 = 0, of rho)
+    combo_pairs<L, T, EQ, FO>(cs, -cf, T(0.5) * cf, T(0), [&](auto IP, auto IM, T ev, T od) {
         constexpr int ip = decltype(IP)::value;
         constexpr int im = decltype(IM)::value;
-        acc(IP, fma_t(cf, h[ip], ev + od));
-        if constexpr (im >= 0) acc(IM, fma_t(cf, h[im], ev - od));
+        constexpr double w = L::wshell(L::shell(ip));
+        acc(IP, fma_t(cf, fma_t(T(-w), cs.drho, h[ip]), ev + od));
+        if constexpr (im >= 0) acc(IM, fma_t(cf, fma_t(T(-w), cs.drho, h[im]), ev - od));
     });
     if constexpr (EQ == 2) {
         T u2 = T(0);
         for (int a = 0; a < L::D; ++a) u2 += cs.ub[a] * cs.ub[a];
         for (int a = 0; a < L::D; ++a) qa[a] -= cs.rho * cs.ub[a] * (T(L::D + 2) + u2);
-        combo_pairs<L, T, 2, 1, true>(cs, T(1), T(0), T(0), [&](auto IP, auto IM, T ev, T od) {
+        combo_pairs<L, T, 2, 1>(cs, T(1), T(0), T(0), [&](auto IP, auto IM, T ev, T od) {
             acc(IP, ev + od);
             if constexpr (decltype(IM)::value >= 0) acc(IM, ev - od);
         });
@@ -918,9 +918,9 @@ __global__ void __launch_bounds__(64)
         cs.om = 0.0;
         cs.cf = 0.0;
         double *es = e + side * (L::Q + 1);
-        // f0 = w rho + (f0 - w rho); the bracket is combo_pairs' NO_BASE part
-        combo_pairs<L, double, EQ, 1, true>(cs, 1.0, 0.0, 0.0, [&](auto IP, auto IM, double ev,
-                                                                 double od) {
+        // f0 = w rho + (f0 - w rho); the bracket is what combo_pairs returns
+        combo_pairs<L, double, EQ, 1>(cs, 1.0, 0.0, 0.0, [&](auto IP, auto IM, double ev,
+                                                           double od) {
             constexpr int ip = decltype(IP)::value;
             constexpr int im = decltype(IM)::value;
             constexpr double w = L::wshell(L::shell(ip));
