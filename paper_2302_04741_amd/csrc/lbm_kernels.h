@@ -182,6 +182,37 @@ template <class L> constexpr double wall_weight(int k)
     return w;
 }
 
+// f(I) for every population, in the order in which combo_pairs hands them out
+template <class L, class F> __device__ __forceinline__ void in_step_order(F &&f)
+{
+    f(std::integral_constant<int, 0>{});
+    static_for<0, ORBITS<L>.n>([&](auto I) {
+        constexpr int i = ORBITS<L>.rep[decltype(I)::value];
+        constexpr Orbit<L> o(i);
+        static_for<0, o.pairs()>([&](auto J) {
+            constexpr int ip = o.plus(i, decltype(J)::value);
+            f(std::integral_constant<int, ip>{});
+            f(std::integral_constant<int, opposite<L>(ip)>{});
+        });
+    });
+}
+
+// The plates' partial sums of one node of row y: ps[c_y + 3] holds the sum of the
+// node's stored deviations with that c_y, added in in_step_order (a step and the pass
+// over a state that no step produced then give the same bits).
+template <class L>
+__device__ __forceinline__ void crossing_sums(const double (&ps)[7], int y, int ny, double rho0,
+                                              double &below, double &above)
+{
+    below = above = 0.0;
+    static_for<1, 4>([&](auto K) {
+        constexpr int k = decltype(K)::value;
+        constexpr double w = wall_weight<L>(k);
+        if (y - k < 0) below += fma_t(w, rho0, ps[3 - k]);
+        if (y + k >= ny) above += fma_t(w, rho0, ps[3 + k]);
+    });
+}
+
 // A plate's densities over the columns (x, z) - (c_x, c_z): the columns' row sums,
 // in order, over the plate's normalisation (side 0: the plate below, 1: above).
 template <class L>
@@ -478,13 +509,8 @@ __device__ __forceinline__ void step_cell(const S *__restrict__ A, S *__restrict
         const int64_t ncol = int64_t(gd.nx) * gd.nz;
         const int64_t col = int64_t(z) * gd.nx + x;
         const int y1 = gd.ny > 3 ? gd.ny - 3 : 0;  // first row of the top plate's sums
-        double below = 0.0, above = 0.0;
-        static_for<1, 4>([&](auto K) {
-            constexpr int k = decltype(K)::value;
-            constexpr double w = wall_weight<L>(k);
-            if (y - k < 0) below += ps[3 - k] + w * co.rho0;
-            if (y + k >= gd.ny) above += ps[3 + k] + w * co.rho0;
-        });
+        double below, above;
+        crossing_sums<L>(ps, y, gd.ny, co.rho0, below, above);
         if (y < 3) wd->part[wall_part_index(wd->par ^ 1, 0, y, ncol, col)] = below;
         if (y >= y1) wd->part[wall_part_index(wd->par ^ 1, 1, y - y1, ncol, col)] = above;
     }
@@ -893,7 +919,7 @@ __global__ void __launch_bounds__(256)
 // wall_mass_kernel: per (x, z) column, plate and row next to the plate, the
 // mass of the crossing slots (populations about to stream into the plate),
 // for a state no step produced (after initialisation or an external write);
-// a step writes the same sums for the state it produces.  The plate's density
+// a step writes the same sums, bit for bit, for the state it produces.  The plate's density
 // rw over a column, at which it re-emits exactly what it absorbs, is the sum
 // of its rows' sums over the normalisation.
 // ---------------------------------------------------------------------------
@@ -946,9 +972,9 @@ __device__ __forceinline__ void wall_column_density(const S *__restrict__ A, con
 {
     // The partial sums of state A (buffer wd.par) over one column: per row next
     // to a plate, its slots whose next move crosses the plate -- rows y = k
-    // with c_y < -k (bottom), rows y = ny-3+k with c_y >= 3 - k (top) --
-    // populations ascending.  Every load is unconditional and independent (the
-    // crossing test only selects the term), so they are all in flight at once.
+    // with c_y < -k (bottom), rows y = ny-3+k with c_y >= 3 - k (top).  Every load
+    // of a row is unconditional and independent (crossing_sums selects the terms),
+    // so they are all in flight at once.
     const int64_t ncol = int64_t(gd.nx) * gd.nz;
     const int x = int(col % gd.nx), z = int(col / gd.nx);
     static_for<0, 2>([&](auto SIDE) {
@@ -959,20 +985,17 @@ __device__ __forceinline__ void wall_column_density(const S *__restrict__ A, con
             const int y = y0 + k;
             if (y >= gd.ny) return;  // uniform: only when ny < 3
             const int64_t own = (int64_t(z) * gd.ny + y) * gd.px + x;
-            double m = 0.0;
-            static_for<0, L::Q>([&](auto I) {
+            double ps[7] = {};
+            in_step_order<L>([&](auto I) {
                 constexpr int i = decltype(I)::value;
                 constexpr int cy = L::c(i, 1);
                 // a slot can cross only toward its plate
-                if constexpr (side == 0 ? cy < 0 : cy > 0) {
-                    const int yd = y + cy;
-                    const double v =
-                        Codec<L, S>::template load<i, double>(A[int64_t(i) * gd.P + own]) +
-                        L::wshell(L::shell(i)) * co.rho0;
-                    m += (side == 0 ? yd < 0 : yd >= gd.ny) ? v : 0.0;
-                }
+                if constexpr (side == 0 ? cy < 0 : cy > 0)
+                    ps[cy + 3] += Codec<L, S>::template load<i, double>(A[int64_t(i) * gd.P + own]);
             });
-            wd.part[wall_part_index(wd.par, side, k, ncol, col)] = m;
+            double below, above;
+            crossing_sums<L>(ps, y, gd.ny, co.rho0, below, above);
+            wd.part[wall_part_index(wd.par, side, k, ncol, col)] = side == 0 ? below : above;
         });
     });
 }
