@@ -1,6 +1,6 @@
 // Index arithmetic of the kernels: unsigned 32-bit division by a divisor fixed at
-// launch, and the periodic wrap of a streaming shift; no HIP dependency (CPU tests
-// check both).
+// launch, the periodic wrap of a streaming shift and quotients by a common divisor; no
+// HIP dependency (CPU tests check them).
 #pragma once
 
 #include <stdint.h>
@@ -50,6 +50,16 @@ __host__ __device__ inline uint32_t wrap_back(uint32_t v, int d, uint32_t n)
     const uint32_t s = d > 0 ? v - m : v + m;
     const uint32_t t = d > 0 ? s + n : s - n;
     return s < t ? s : t;
+}
+
+// m / d, correctly rounded, for several m over one d: inv is 1.0 / d, correctly rounded,
+// and one correction of m inv with the exact remainder gives the rounded quotient
+// (Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990).  Finite m and d, d and the quotient normal.
+__host__ __device__ inline double quotient(double m, double d, double inv)
+{
+    const double q = m * inv;
+    return __builtin_fma(__builtin_fma(-q, d, m), inv, q);
 }
 
 }  // namespace lbm

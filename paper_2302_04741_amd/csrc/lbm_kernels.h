@@ -222,7 +222,7 @@ __device__ __forceinline__ void wall_densities_of(const WallDesc &wd, const Grid
 {
     const int64_t ncol = int64_t(gd.nx) * gd.nz;
     const double *rows = wd.part + wall_part_index(wd.par, side, 0, ncol, 0);
-    const double inv = 1.0 / wd.e[side * (L::Q + 1) + L::Q];
+    const double norm = wd.e[side * (L::Q + 1) + L::Q], inv = 1.0 / norm;
     static_for<0, WALL_SHIFTS<L>.n>([&](auto K) {
         constexpr int k = decltype(K)::value;
         constexpr int cx = WALL_SHIFTS<L>.cx[k], cz = WALL_SHIFTS<L>.cz[k];
@@ -232,7 +232,7 @@ __device__ __forceinline__ void wall_densities_of(const WallDesc &wd, const Grid
         double m = rows[col];
         if (gd.ny > 1) m += rows[ncol + col];
         if (gd.ny > 2) m += rows[2 * ncol + col];
-        rw[k] = m * inv;
+        rw[k] = quotient(m, norm, inv);
     });
 }
 
