@@ -192,16 +192,19 @@ bool capturing(hipStream_t stream)
     return st != hipStreamCaptureStatusNone;
 }
 
-// Whether a kernel on the current device can address p: memory of this device.
-bool on_this_device(const void *p)
+// Whether both are memory of the current device, so that a kernel launched there can
+// address them.
+bool both_on_this_device(const void *p, const void *q)
 {
-    hipPointerAttribute_t a;
+    hipPointerAttribute_t a, b;
     int dev = -1;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+        hipPointerGetAttributes(&b, q) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();  // an address the runtime does not know is no error here
         return false;
     }
-    return a.type == hipMemoryTypeDevice && a.device == dev;
+    return a.type == hipMemoryTypeDevice && a.device == dev && b.type == hipMemoryTypeDevice &&
+           b.device == dev;
 }
 
 // The dense planes out of the handle's current buffer (exporting) or into it.
@@ -210,7 +213,8 @@ bool on_this_device(const void *p)
 // padding it is one contiguous run, 6.1 TB/s) and falls to 1-3 TB/s on others, where
 // the row kernel keeps 3-6 TB/s (D2Q37 1017^2 FP32 49 us against 108).  Small states
 // keep it too (130^2 FP32, 2.5 MB: 3.5 us against 4.1), and it takes what the kernel
-// cannot: memory of another device, or not aligned to the stored type.
+// cannot: memory of another device (the handle's, or the caller's), or not aligned to the
+// stored type.
 constexpr size_t ROW_KERNEL_MIN_BYTES = size_t(6) << 20;
 
 hipError_t copy_populations(const lbm_sim *s, void *dense, bool exporting)
@@ -219,7 +223,8 @@ hipError_t copy_populations(const lbm_sim *s, void *dense, bool exporting)
     const size_t row = size_t(s->gd.nx) * sb;
     if (s->gd.px != s->gd.nx && (row % 16 != 0 || row < 1024) &&
         lbm_population_bytes(s) >= ROW_KERNEL_MIN_BYTES &&
-        reinterpret_cast<uintptr_t>(dense) % sb == 0 && on_this_device(dense))
+        reinterpret_cast<uintptr_t>(dense) % sb == 0 &&
+        both_on_this_device(dense, s->pop[s->cur]))
         return launch_copy_rows(s->p.storage, s->pop[s->cur], dense, s->gd, s->Q, exporting,
                                 s->stream);
     const size_t width = size_t(s->gd.nx) * sb, pitch = size_t(s->gd.px) * sb;
