@@ -29,7 +29,10 @@ def _as_device(torch, a, shape, device, stream, keep):
         t = a.to(device=device, dtype=torch.float64).reshape(shape).contiguous()
     else:
         arr = np.asarray(a, dtype=np.float64)
-        if arr.shape != tuple(shape) or not (arr.flags.c_contiguous and arr.flags.writeable):
+        # torch takes contiguous arrays as they are, but for read-only ones and for the
+        # strides an extent of 1 can have (negative, or not whole elements)
+        if arr.shape != tuple(shape) or not (arr.flags.c_contiguous and arr.flags.writeable) or \
+                any(st < 0 or st % arr.itemsize for st in arr.strides):
             arr = np.ascontiguousarray(np.broadcast_to(arr, shape)).copy()
         # (a blocking copy: the caller's array is read before this returns)
         t = torch.from_numpy(arr).to(device=device, non_blocking=False)
