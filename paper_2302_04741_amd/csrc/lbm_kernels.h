@@ -346,7 +346,11 @@ struct StepShape {
 // D2Q37 2048^2 220 / 226, 3000^2 475 / 500; below that size it gains or loses 2%,
 // and F16, with half the bytes a wavefront, loses (256^3 700 / 496); F16 of 1 GiB a
 // buffer and more takes 512 threads unlimited (256^3 476 / 490, D2Q37 4096^2 441 /
-// 458; below it is within 2% either way).
+// 458; below it is within 2% either way).  FP64 on D3Q39 from 1 GiB a buffer: 256
+// threads and 8 wavefronts a CU (against 128 threads, 12 wavefronts: 160^3 452 / 459,
+// 224^3 1280 / 1337, 256^3 1902 / 1934, 280^3 2527 / 2637, 320^3 3803 / 3856, 64x300x250
+// 534 / 530; 256 threads unlimited 459, 1306, 1934, 2645, 3960); below it, and on D2Q37,
+// within 2% either way.
 constexpr int64_t STEP_LARGE_BYTES = 400 * MIB;
 constexpr unsigned STEP_LDS_PER_CU = 160u << 10;
 
@@ -386,9 +390,10 @@ inline StepShape step_shape(int64_t buffer_bytes, int64_t waves, int threads)
     int bx = threads;
     if (bx <= 0 && buffer_bytes <= STEP_CACHED_BYTES) bx = small_grid_threads<LAT, S>(waves);
     const bool wide = large || (sizeof(S) == 2 && buffer_bytes >= 1024 * MIB);
-    if (bx <= 0) bx = sizeof(S) == 8 ? 128 : (wide ? 512 : 256);
+    const bool large64 = LAT == 1 && sizeof(S) == 8 && buffer_bytes >= 1024 * MIB;
+    if (bx <= 0) bx = sizeof(S) == 8 ? (large64 ? 256 : 128) : (wide ? 512 : 256);
     bx = bx < step_max_threads<S>() ? bx : step_max_threads<S>();
-    const bool limit = large && (bx == 256 || bx == 512);
+    const bool limit = (large || large64) && (bx == 256 || bx == 512);
     return StepShape{bx, limit ? STEP_LDS_PER_CU * unsigned(bx) / 512u : 0u};
 }
 
