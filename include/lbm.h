@@ -315,7 +315,8 @@ LBM_API lbm_status lbm_batch_set(lbm_batch *b, lbm_sim *const *sims, int32_t cou
 LBM_API lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps);
 
 /* Launch shape of the multi-grid kernel (an implementation choice).  threads: threads per block, 64, 128
- * or 256 (0 = 128), i.e. 1, 2 or 4 tiles per block; blocks: 0 = enough blocks
+ * or 256 (0 = the default: 128, in FP64 256 for lists of some 450 to 700 tiles),
+ * i.e. 1, 2 or 4 tiles per block; blocks: 0 = enough blocks
  * for one wavefront per tile (default), > 0 = a persistent grid of that many
  * blocks (at most 2^31 - 1).  Results do not depend on the shape.  Graphs
  * captured before must be captured again. */
@@ -342,7 +343,7 @@ LBM_API void lbm_batch_destroy(lbm_batch *b);
  *   sims: 1..LBM_NOALLOC_MAX_SIMS distinct handles sharing lattice, storage,
  *         eq_order and force_order (grids, tau_hat, mu, forces and plates may
  *         differ); count above the maximum is LBM_EINVAL.  Launch shape: that
- *         of a default batch (128 threads, one wavefront per 64-cell tile), so
+ *         of a default batch (one wavefront per 64-cell tile), so
  *         every member's result is bitwise the one lbm_batch_step gives.
  *   hip_stream: the stream of every launch (NULL = the null stream); the
  *         current device must be the members' device.  As with lbm_batch_step,

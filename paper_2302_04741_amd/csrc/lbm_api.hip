@@ -888,7 +888,7 @@ struct lbm_batch {
     std::vector<int64_t> gen_at_set;   // members' launch-argument generations then
     int64_t generation;                // bumped whenever the table or launch shape changes
     int64_t steps_done;                // batch steps since the table was built
-    int threads;     // threads per block (tiles of 64 cells, one per wavefront)
+    int threads;     // threads per block (tiles of 64 cells, one per wavefront), 0: default
     int64_t blocks;  // 0: one block per tile
     bool walls;           // some member has plates
 };
@@ -906,10 +906,6 @@ struct lbm_graph {
 };
 
 namespace {
-// What the header states.  64 / 128 / 256 threads: 17.8k / 19.1k / 19.7k MLUPS on 64 grids of
-// 64^2 to 1024^2 FP32, 17.4k / 18.3k / 19.1k on 64 of 32^2 to 256^2.
-constexpr int BATCH_DEFAULT_THREADS = 128;
-
 size_t batch_begin_bytes(int32_t max_sims) { return align_up(size_t(max_sims + 1) * 8); }
 
 lbm_status batch_check(const lbm_batch *b)
@@ -1014,7 +1010,7 @@ lbm_status lbm_batch_create(int32_t max_sims, void *workspace, size_t workspace_
     b->table = reinterpret_cast<TileSim *>(b->ws + batch_begin_bytes(max_sims));
     b->steps_done = 0;
     b->generation = 0;
-    b->threads = BATCH_DEFAULT_THREADS;
+    b->threads = 0;
     b->blocks = 0;
     b->walls = false;
     *out = b;
@@ -1063,7 +1059,7 @@ lbm_status lbm_batch_set_launch(lbm_batch *b, int32_t threads, int64_t blocks)
     if (blocks < 0 || blocks > 0x7fffffff)
         return fail(LBM_EINVAL, "blocks must be in [0, 2^31 - 1]");
     // the tiles do not depend on the launch shape: the table stays as it is
-    b->threads = threads ? threads : BATCH_DEFAULT_THREADS;
+    b->threads = threads;
     b->blocks = blocks;
     b->generation++;  // graphs captured with the old shape are stale
     return ok();
@@ -1143,7 +1139,6 @@ lbm_status lbm_batch_step_noalloc(lbm_sim *const *sims, int32_t count, int64_t n
     BatchLaunch bl{};
     bl.begin = begin;
     bl.table = table;
-    bl.threads = BATCH_DEFAULT_THREADS;
     bl.stream = stream;
     e = upload_table(sims, count, begin, table, stream, bl.walls);
     if (e != hipSuccess) return dev_fail(e, "tile table fill launch");

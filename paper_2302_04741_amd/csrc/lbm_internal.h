@@ -816,7 +816,7 @@ struct BatchLaunch {
     int64_t tile0;          // the first member's first tile
     int64_t ntiles;         // tiles of these members
     int parity;             // batch steps since the table was built, mod 2
-    int threads;            // threads per block (64, 128 or 256): 1, 2 or 4 tiles
+    int threads;            // threads per block (64, 128 or 256: 1, 2 or 4 tiles), 0: default
     int64_t blocks;         // 0: one block per tile; > 0: persistent walk
     hipStream_t stream;
     bool walls;             // some member of the batch has plates (the kernel variant)

@@ -115,13 +115,27 @@ hipError_t launch_pattern_ls(const void *A, void *B, const GridDims &gd, const L
     });
 }
 
+// Default block of the multi-grid step: 128 threads.  64 / 128 / 256: 17.8k / 19.1k / 19.7k
+// MLUPS on 64 grids of 64^2 to 1024^2 FP32, 17.4k / 18.3k / 19.1k on 64 of 32^2 to 256^2.
+// FP64 lists of 449 to 704 tiles: 256, four wavefronts of a block on the four SIMDs of a CU
+// and at most one block a CU (us a step, against 128: 456 tiles 6.1 / 6.8, 510 7.7 / 8.1, 538
+// 8.2 / 8.8, 598 8.5 / 9.4, 640 8.1 / 8.3, 704 8.3 / 8.8; 448 tiles 7.0 / 6.8, 760 9.9 / 9.9,
+// 860 9.5 / 9.0).
+template <class S> inline int multi_step_threads(int64_t tiles)
+{
+    return sizeof(S) == 8 && tiles > 448 && tiles <= 704 ? 256 : 128;
+}
+
 template <int LAT, class S>
 hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
 {
     if (bl.ntiles <= 0) return hipSuccess;
+    const int threads = bl.threads > 0    ? bl.threads
+                        : bl.blocks > 0 ? 128
+                                        : multi_step_threads<S>(bl.ntiles);
     // one wavefront per tile, or the persistent grid; the kernel strides over
     // the list, so a grid capped at 2^31 - 1 blocks still covers every tile
-    const int64_t wpb = bl.threads / 64;
+    const int64_t wpb = threads / 64;
     const int64_t need = (bl.ntiles + wpb - 1) / wpb;
     int64_t grid = bl.blocks > 0 ? std::min(bl.blocks, need) : need;
     grid = std::min<int64_t>(grid, 0x7fffffff);
@@ -132,19 +146,19 @@ hipError_t launch_multi_step_ls(int eq, int fo, const BatchLaunch &bl)
     // 1168, 32 of them, 1.4 GB, 519 / 526, four D3Q39 128^3 476 / 503; 16 grids, 974 MB,
     // 370 / 366: the last round of blocks counts there)
     const bool limit = sizeof(S) == 4 && bl.blocks <= 0 && bl.bytes >= 1024 * MIB;
-    const unsigned lds = limit ? STEP_LDS_PER_CU * unsigned(bl.threads) / 512u : 0u;
+    const unsigned lds = limit ? STEP_LDS_PER_CU * unsigned(threads) / 512u : 0u;
     return with_eq_fo<LAT>(eq, fo, [&](auto E, auto O) {
         constexpr int EQ = decltype(E)::value, FO = decltype(O)::value;
         if (bl.walls)
             return with_wall_policy(sp.policy, [&](auto P) {
                 hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, true>),
-                                   dim3(unsigned(grid)), dim3(unsigned(bl.threads)), 0, bl.stream,
+                                   dim3(unsigned(grid)), dim3(unsigned(threads)), 0, bl.stream,
                                    bl.begin, bl.table, bl.nsims, bl.ntiles, sw);
                 return hipGetLastError();
             });
         return with_policy<LAT, S>(sp.policy, [&](auto P) {
             hipLaunchKernelGGL((multi_step_kernel<LAT, S, EQ, FO, decltype(P)::value, false>),
-                               dim3(unsigned(grid)), dim3(unsigned(bl.threads)), lds, bl.stream,
+                               dim3(unsigned(grid)), dim3(unsigned(threads)), lds, bl.stream,
                                bl.begin, bl.table, bl.nsims, bl.ntiles, sw);
             return hipGetLastError();
         });

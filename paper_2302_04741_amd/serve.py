@@ -175,7 +175,8 @@ class Server:
     next chunk to run while the host retires finished requests (totals checked,
     slot and memory released) and admits new ones.
 
-    launch: "default" (128 threads, one wavefront per 64-cell tile), "tuned"
+    launch: "default" (128 threads, in FP64 for some list lengths 256, one
+    wavefront per 64-cell tile), "tuned"
     (the autotuner's choice for the batch class, tuned on first use and cached),
     or a (threads, blocks) pair applied to every batch.  check_every: chunks
     between the conservation checks of running members (finishing members are
@@ -312,7 +313,8 @@ class Server:
                             cur_launch = want
                         batch.set(sims)
                         members = ids
-                    key = "%d threads, %s" % (cur_launch[0] or 128,
+                    default = "128 or 256" if self.storage == "f64" else "128"
+                    key = "%s threads, %s" % (cur_launch[0] or default,
                                               "one wavefront per tile" if cur_launch[1] == 0
                                               else "persistent, %d blocks" % cur_launch[1])
                     self.launches_used[key] = self.launches_used.get(key, 0) + 1

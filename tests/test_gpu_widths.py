@@ -1,7 +1,8 @@
-"""Single grids larger than the memory-side cache: results do not depend, bit for bit, on
-the width of the step's blocks.  The width moves the line between the part of a sweep
-whose stores are streamed and the part whose stores are kept, which are two compilations
-of the same update; the default of each size is one of the widths."""
+"""Results do not depend, bit for bit, on the width of the blocks.
+
+Single grids larger than the memory-side cache: the width moves the line between the part
+of a sweep whose stores are streamed and the part whose stores are kept, which are two
+compilations of the same update; the default of each size is one of the widths."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -39,3 +40,27 @@ def test_every_width_gives_the_same_bits(lattice, storage, dims):
         else:
             assert torch.equal(got, want), threads
     s.close()
+
+
+# tiles of the FP64 lists around the lines between which the default is 256 threads
+@pytest.mark.parametrize("sides", [(64,) * 7, (64,) * 7 + (2,), (52, 162), (64,) * 11,
+                                   (64,) * 11 + (2,)])
+def test_batch_default_width_gives_the_same_bits(sides):
+    import torch
+
+    from paper_2302_04741_amd import sim, workloads
+
+    got = []
+    for threads in (0, 64, 128, 256):
+        sims = [sim.from_workload(workloads.thermal_shear_2d(n=n), storage="f64") for n in sides]
+        b = sim.Batch(len(sims))
+        b.set(sims)
+        if threads:
+            b.set_launch(threads, 0)
+        b.step(3)
+        got.append([s.get_populations() for s in sims])
+        b.close()
+        for s in sims:
+            s.close()
+    for other in got[1:]:
+        assert all(torch.equal(a, c) for a, c in zip(got[0], other))
