@@ -19,19 +19,26 @@ inline FieldShape field_shape(const GridDims &gd, unsigned threads, unsigned lds
     const int64_t waves = ((int64_t(gd.nx) + 63) / 64) * gd.ny * gd.nz, wpb = threads / 64;
     return FieldShape{dim3(unsigned((waves + wpb - 1) / wpb)), dim3(threads), lds};
 }
-// Reading kernels: 256 threads; the FP32 moments of large grids 12 wavefronts a CU
-// (D3Q39 256^3 603 us against 624; FP64 and F16 within 2% either way).
+// The LDS a block asks for so that `blocks` of them share a CU: a third of the LDS does
+// not fit three times once it is rounded up, so the request is rounded down (to 4 KiB).
+inline unsigned lds_for_blocks(unsigned blocks) { return STEP_LDS_PER_CU / blocks / 4096u * 4096u; }
+// Reading kernels: 256 threads; the FP32 moments of large grids 8 wavefronts a CU (us,
+// against 12 and unlimited: D3Q39 160^3 152 / 152 / 155, 200^3 317 / 323 / 332, 256^3 611 /
+// 601 / 620, D2Q37 3001x2999 309 / 315 / 320; FP64 and F16 within 2% either way).
 template <int LAT, class S> inline FieldShape moments_shape(const GridDims &gd)
 {
     const bool large = sizeof(S) == 4 && buffer_lines_bytes<LAT, S>(gd) >= STEP_LARGE_BYTES;
-    return field_shape(gd, 256, large ? STEP_LDS_PER_CU / 3 : 0u);
+    return field_shape(gd, 256, large ? lds_for_blocks(2) : 0u);
 }
 // Scattering kernels (their shifted rows' lines are completed by neighbouring
 // wavefronts, in the L2 of one XCD if one block holds the whole row): whole rows
 // while 8 wavefronts do (4 on small grids), and on large grids few enough blocks
-// that the lines are complete before they leave the L2.  us, against 256 threads:
-// D3Q39 FP32 160^3 159 / 211, 256^3 589 / 675; FP64 129x95x110 150 / 156, D2Q37
-// 1537x1021 129 / 137; F16 256^3 375 / 416.
+// that the lines are complete before they leave the L2: as many whole blocks as 12
+// wavefronts a CU allow, 16 in F16 (rows of 5 wavefronts run 10 and 15, of 7, 7 and 14,
+// of 8 and more, 8 and 16).  us, against 256 threads: D3Q39 FP32 160^3 159 / 211, 256^3
+// 589 / 675; FP64 129x95x110 150 / 156, D2Q37 1537x1021 129 / 137; F16 256^3 375 / 416.
+// F16 rows of 5 wavefronts, 15 a CU against 10: 320x256x200 385 / 402, the rebuild 538 /
+// 605, 300x256x256 620 / 618, 821 / 849.
 template <int LAT, class S> inline FieldShape scatter_shape(const GridDims &gd)
 {
     const unsigned k = unsigned((gd.nx + 63) / 64);  // wavefronts a row
@@ -39,7 +46,7 @@ template <int LAT, class S> inline FieldShape scatter_shape(const GridDims &gd)
     const unsigned w = k <= most ? k * (most / k) : most;
     const bool large = buffer_lines_bytes<LAT, S>(gd) >= STEP_LARGE_BYTES;
     const unsigned per_cu = (sizeof(S) == 2 ? 16u : 12u) / w;
-    return field_shape(gd, 64 * w, large ? STEP_LDS_PER_CU / per_cu : 0u);
+    return field_shape(gd, 64 * w, large ? lds_for_blocks(per_cu) : 0u);
 }
 
 template <int LAT, class F> hipError_t with_eq_fo(int eq, int fo, F &&f)
