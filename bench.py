@@ -509,10 +509,11 @@ def main(argv=None) -> int:
         e1.record(stream)
         torch.cuda.synchronize()
         rep_ms.append(e0.elapsed_time(e1) / args.steps)
-    # the ceiling of the step's access pattern: the same traffic without the
-    # arithmetic (lbm_pattern_pass), at each block size, the best one kept (at
-    # the step's own shape the bare pattern can be slower than the step: with
-    # no arithmetic between them, more loads and stores are in flight at once)
+    # the step's traffic without the arithmetic (lbm_pattern_pass), at each block
+    # size, the best one kept (at the step's own shape the bare pattern can be
+    # slower than the step: with no arithmetic between them, more loads and stores
+    # are in flight at once; and it sweeps in one direction, so it takes nothing
+    # from the memory-side cache, as the step does)
     pat_ms = {}
     if args.repeats > 0:
         for blk in PATTERN_BLOCKS:
@@ -597,8 +598,8 @@ def main(argv=None) -> int:
         pat = max(by_block.values())
         out["pattern_ceiling"] = {
             "achieved": pat, "unit": "GB/s",
-            "what": "the step's loads and stores alone, no arithmetic (lbm_pattern_pass), "
-                    "best over block sizes, %d passes each" % args.steps,
+            "what": "the step's loads and stores alone, no arithmetic, one direction "
+                    "(lbm_pattern_pass), best over block sizes, %d passes each" % args.steps,
             "by_block": by_block,
             "step_frac": round(achieved / pat, 4),
         }

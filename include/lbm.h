@@ -211,9 +211,12 @@ LBM_API lbm_status lbm_round_f16_stochastic(const float *v, const uint32_t *seed
  * pull source x - c_i and written back unchanged at the cell's own slot of
  * the idle population buffer, with the step's work split and launch shape but
  * none of its arithmetic.  The state, the step count and everything a later
- * call reads are unchanged (a step overwrites the idle buffer whole).  Timing
- * it beside lbm_step gives the ceiling of the step's access pattern on the
- * device.  Async on the handle's stream; LBM_EINVAL if repeats < 0. */
+ * call reads are unchanged (a step overwrites the idle buffer whole).  Every
+ * pass runs through the grid in one direction and, where the step streams its
+ * stores, streams all of them, so timing it beside lbm_step gives the rate of
+ * the step's accesses from and to memory; a step that finds part of its state in
+ * the memory-side cache passes it.  Async on the handle's stream; LBM_EINVAL if
+ * repeats < 0. */
 LBM_API lbm_status lbm_pattern_pass(lbm_sim *s, int64_t repeats);
 
 /* Raw population state for checkpoint/restart (the stored f~_i of eq. (lbm),
@@ -361,9 +364,11 @@ LBM_API lbm_status lbm_batch_step_noalloc(lbm_sim *const *sims, int32_t count, i
  * batch (b) --
  * exactly one of them non-NULL -- into a HIP graph on its stream, which must
  * not be the null stream.  Capturing executes nothing and leaves the state
- * unchanged.  The graph holds the buffers of the handle: it stays valid while
- * the handle lives and is not re-initialised (lbm_set_force before the first
- * step rebuilds in place, so it is fine; a new lbm_batch_set is not). */
+ * unchanged.  The graph holds the buffers and the launch arguments of the handle:
+ * it stays valid while the handle lives and nothing that those depend on is
+ * changed; lbm_graph_launch refuses (LBM_EINVAL) after a new force, viscosity,
+ * block width, stream or set of plates, a new lbm_batch_set or launch shape, and
+ * from the other buffer (an odd number of steps since). */
 LBM_API lbm_status lbm_graph_create(lbm_sim *s, lbm_batch *b, int64_t nsteps, lbm_graph **out);
 
 /* Replay the captured steps of eq. (lbm) `repeats` times (asynchronous on the

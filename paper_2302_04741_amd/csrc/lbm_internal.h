@@ -92,6 +92,11 @@ template <> struct CacheBits<Policy::KEEP> {
     static constexpr int load = BUF_NT, store = BUF_THROUGH;
 };
 
+// The LLVM intrinsics by name (a compiler without them fails at the link).  clang's
+// builtins take a resource that only __builtin_amdgcn_make_buffer_rsrc forms, which masks
+// the address on every access: one scalar instruction more each, 0.2-0.4% of a step, and
+// 20 to 28 bytes of scratch in the FP64 D3Q39 step (129x95x110, 8 steps, 1565 us against
+// 1525; 256^3 1940 against 1887).
 typedef int RsrcWords __attribute__((ext_vector_type(4)));
 typedef int Words2 __attribute__((ext_vector_type(2)));
 __device__ float buf_load_f32(RsrcWords, int, int, int) __asm("llvm.amdgcn.raw.buffer.load.f32");

@@ -602,8 +602,9 @@ __global__ void __launch_bounds__(step_max_threads<S>())
 
 // K7 (diagnostic): the memory traffic of K1 alone -- every population read
 // from its pull source and written unchanged at the cell's own slot of the
-// other buffer, K1's work split, no arithmetic.  Its rate is the ceiling of
-// K1's access pattern on the device.
+// other buffer, K1's work split, no arithmetic.  Every pass sweeps forward and, above
+// the cached size, streams every store: the rate of K1's loads and stores from and to
+// memory.  K1 passes it where the memory-side cache serves part of its reads (see Policy).
 template <int LAT, class S, Policy P>
 __global__ void __launch_bounds__(step_max_threads<S>())
     pattern_kernel(const S *__restrict__ A, S *__restrict__ B, GridDims gd)

@@ -69,8 +69,8 @@ template <int LAT, class S, class F> hipError_t with_policy(Policy p, F &&f)
     }
     return f(std::integral_constant<Policy, Policy::STREAM>{});
 }
-// The same for the kernels with plates, whose larger grids stream every store, in
-// one direction (channels are small).
+// The same for the kernels with plates, whose larger grids stream every store: K1c in one
+// direction (channels are small), the plated batch kernel in both, as the periodic one.
 template <class F> hipError_t with_wall_policy(Policy p, F &&f)
 {
     if (p == Policy::RESIDENT) return f(std::integral_constant<Policy, Policy::RESIDENT>{});

@@ -246,8 +246,8 @@ class Sim:
 
     def pattern_pass(self, repeats: int = 1):
         """Diagnostic: `repeats` passes of the step's memory traffic without its
-        arithmetic (the state is unchanged); its rate is the ceiling of the
-        step's access pattern."""
+        arithmetic, in one direction (the state is unchanged): the rate of the
+        step's accesses from and to memory."""
         check(load().lbm_pattern_pass(self.handle, int(repeats)))
 
     def set_viscosity(self, mu: float):
