@@ -268,7 +268,7 @@ template <class L, class S> struct PullOffsets {
 // a uniform test for each c_y; the densities' and the other populations' loads are
 // all in flight before the first emission is formed.  (A test, three dependent
 // loads and a division for each slot made the row wavefronts of the plated 3 x 150
-// FP64 channel twice as long as the others': 10.6 -> 6.2 us a step, 8254 -> 2586
+// FP64 channel twice as long as the others': 10.6 -> 6.1 us a step, 8254 -> 2671
 // instructions in the kernel.)
 template <class L, class S, class T, bool WALLS = false, int LD = BUF_DEFAULT>
 __device__ __forceinline__ void gather(const S *__restrict__ A, const GridDims &gd, int x, int y,
